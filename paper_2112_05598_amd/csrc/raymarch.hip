@@ -170,6 +170,7 @@ struct Corners {
     int v;          // lower corner voxel
     int i[3];       // lower corner coordinates
     float f[3];     // fractional position inside the cell
+    float g[3];     // clamped grid coordinates
     float w[8];     // weights, corner j = (j&1, j>>1&1, j>>2) offsets
 };
 
@@ -181,6 +182,7 @@ __device__ __forceinline__ void corners(const Geo& G, const float g[3], Corners&
         const float gc = fminf(fmaxf(g[a], 0.0f), (float)(n[a] - 1));
         const int i0 = min((int)gc, n[a] - 2);
         c.i[a] = i0;
+        c.g[a] = gc;
         f[a] = gc - (float)i0;
         c.f[a] = f[a];
     }
@@ -197,15 +199,6 @@ __device__ __forceinline__ void corners(const Geo& G, const float g[3], Corners&
     c.w[5] = wx1 * a01;
     c.w[6] = wx0 * a11;
     c.w[7] = wx1 * a11;
-}
-
-// the lower-corner voxel corners() would give for the grid coordinates g
-__device__ __forceinline__ int cell_key(const Geo& G, const float g[3]) {
-    const int n[3] = {G.nx, G.ny, G.nz};
-    int i[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) i[a] = min((int)fminf(fmaxf(g[a], 0.0f), (float)(n[a] - 1)), n[a] - 2);
-    return (i[2] * G.ny + i[1]) * G.nx + i[0];
 }
 
 __device__ __forceinline__ int corner_off(int j, int nx, int nxy) { return (j & 1) + ((j >> 1) & 1) * nx + (j >> 2) * nxy; }
@@ -292,15 +285,25 @@ __device__ __forceinline__ float dpp_xor1(float v) { return __int_as_float(dpp_x
 __device__ __forceinline__ float dpp_row_xor8(float v) { return __int_as_float(dpp_row_xor8(__float_as_int(v))); }
 
 // ------------------------------------------------------------------ wave helpers
+// minimum / maximum over the wave: inside each row of 16 lanes by DPP rotations, then over the
+// four rows in scalar registers
+template <int N>
+__device__ __forceinline__ int dpp_ror(int v) { return __builtin_amdgcn_mov_dpp(v, 0x120 + N, 0xF, 0xF, true); }
 __device__ __forceinline__ int wave_min_i(int v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-    return v;
+    v = min(v, dpp_ror<8>(v));
+    v = min(v, dpp_ror<4>(v));
+    v = min(v, dpp_ror<2>(v));
+    v = min(v, dpp_ror<1>(v));
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 __device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-    return v;
+    v = max(v, dpp_ror<8>(v));
+    v = max(v, dpp_ror<4>(v));
+    v = max(v, dpp_ror<2>(v));
+    v = max(v, dpp_ror<1>(v));
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 __device__ __forceinline__ float wave_min_f(float v) {
 #pragma unroll
@@ -334,52 +337,32 @@ constexpr int kB = 8;
 constexpr int kB3 = kB * kB * kB;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ f4 dpp_xor1(f4 v) { return f4{dpp_xor1(v.x), dpp_xor1(v.y), dpp_xor1(v.z), dpp_xor1(v.w)}; }
-__device__ __forceinline__ f4 dpp_row_xor8(f4 v) {
-    return f4{dpp_row_xor8(v.x), dpp_row_xor8(v.y), dpp_row_xor8(v.z), dpp_row_xor8(v.w)};
+typedef float f16v __attribute__((ext_vector_type(16)));
+// value of lane K of the own row of 16 lanes, and of the lane N before it (rotating in the row)
+template <int K>
+__device__ __forceinline__ float dpp_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + K, 0xF, 0xF, true));
 }
+template <int N>
+__device__ __forceinline__ float dpp_ror(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xF, 0xF, true));
+}
+// orders a wave's LDS accesses for the compiler (one wave's LDS accesses execute in order)
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+constexpr int kStageRow = 68;  // 16 float4 of a row and 4 floats of padding: the rows' reads hit different banks
 
-// Folding of a 2x2 lane quad before an election: a lane hands its value to its x neighbour
-// (lane ^ 1), then to its y neighbour (lane ^ 8), then across the quad's diagonal (lane ^ 9),
-// each time when both are still in the election and sit in the same cell (same key); the
-// higher lane of a pair gives.  Every lane of the wave must run it (DPP swaps).
-struct QuadFolds {
-    bool give_x, give_y, give_d, keep;
-};
-__device__ __forceinline__ QuadFolds quad_folds(bool mine, int cell) {
-    const int lane = lane_id();
-    const int key = mine ? cell : -1;
-    QuadFolds q;
-    q.give_x = mine & (dpp_xor1(key) == key) & ((lane & 1) != 0);
-    const bool keep_x = mine & !q.give_x;
-    const int k2 = keep_x ? key : -1;
-    q.give_y = keep_x & (dpp_row_xor8(k2) == k2) & ((lane & 8) != 0);
-    const bool keep_y = keep_x & !q.give_y;
-    const int k3 = keep_y ? key : -1;
-    q.give_d = keep_y & (dpp_row_xor8(dpp_xor1(k3)) == k3) & ((lane & 8) != 0);
-    q.keep = keep_y & !q.give_d;
-    return q;
-}
 // explicit LDS pointers, so accesses compile to ds_* instructions rather than flat ones
 #define LDS __attribute__((address_space(3)))
 typedef LDS f4 lds_f4;
-typedef LDS f2 lds_f2;
 typedef LDS float lds_float;
 typedef LDS int lds_int;
-typedef LDS unsigned char lds_u8;
 
 __device__ __forceinline__ int ring_slot(int x, int y, int z) {
     return ((z & (kB - 1)) * kB + (y & (kB - 1))) * kB + (x & (kB - 1));
 }
-
-// Corner order of the elected scatters.  The 2x2 lane quad to the right of another visits corner
-// k + 2 in the round where that one visits corner k, the quad below it corner k + 1.  Two
-// face-adjacent cells then never update one voxel in the same round, except when the right-hand
-// quad's cell lies at -y or the lower quad's at -x; mirroring the corners' y offset when the
-// camera's right vector points to -y, and their x offset when its down vector points to -x,
-// removes those cases.  This mask holds the mirrored axes.
-__device__ __forceinline__ int corner_mask(const DevCam& c) { return (c.R[1] < 0.0f ? 1 : 0) | (c.R[3] < 0.0f ? 2 : 0); }
 
 // Window bookkeeping shared by the accumulator kinds: origin, fit and slab iteration.
 struct Window {
@@ -420,180 +403,294 @@ struct Window {
         }
         o[a] = no;
     }
-    // Make the window cover the corner boxes [lo, hi] of every lane that is on.
-    template <class Flush>
-    __device__ __forceinline__ void fit(bool on, const int lo[3], const int hi[3], Flush& flush) {
+    // New origin `no` that covers the corner boxes [lo, hi] of every lane that is on; false if the
+    // window covers them already.
+    __device__ __forceinline__ bool target(bool on, const int lo[3], const int hi[3], int no[3]) const {
         const bool fits = !on || inside(lo, hi);
-        if (!wave_any(!fits)) return;
+        if (!wave_any(!fits)) return false;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const int mn = wave_min_i(on ? lo[a] : (1 << 30));
             const int mx = wave_max_i(on ? hi[a] : -(1 << 30));
+            no[a] = o[a];
             if (mn > mx) continue;  // no lane on
-            int no = o[a];
             if (mx - mn < kB) {
-                if (mn < no) no = mn;
-                else if (mx > no + kB - 1) no = mx - kB + 1;
-            } else if (mn < no || mn > no + kB - 1) {
-                no = mn;  // cannot cover every lane: keep the low end, the rest go to HBM
+                if (mn < no[a]) no[a] = mn;
+                else if (mx > no[a] + kB - 1) no[a] = mx - kB + 1;
+            } else if (mn < no[a] || mn > no[a] + kB - 1) {
+                no[a] = mn;  // cannot cover every lane: keep the low end, the rest go to HBM
             }
-            move_axis(a, no, flush);
         }
+        return true;
+    }
+    // Make the window cover the corner boxes [lo, hi] of every lane that is on.
+    template <class Flush>
+    __device__ __forceinline__ void fit(bool on, const int lo[3], const int hi[3], Flush& flush) {
+        int no[3];
+        if (!target(on, lo, hi, no)) return;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) move_axis(a, no[a], flush);
     }
 };
 
-// The J^T accumulator: float4 (three colour channels and sigma) per window voxel.  LDS
-// float atomics are slow on this hardware even without address conflicts, so updates are
-// plain read-modify-writes by one elected lane per slot: every pending lane writes its lane
-// id into the slot's tag and reads the tag and the slot back in one batch; the lanes that
-// read their own id own a distinct slot this round and write the sum, the others retry.
-// Lanes of one cell are folded into one (quad_folds); lanes of neighbouring cells visit
-// the corners in orders chosen so that they target different voxels in the same round.
+// The J^T accumulator: float4 (three colour channels and sigma) per window voxel, fed by the
+// matrix cores.  Row q of a wave (lanes 16q .. 16q + 15) marches a patch of 4x4 pixels.  The
+// patch keeps the sums of a 4x4x4 voxel box in registers, four per lane.  A sample's
+// contribution to a voxel factors into (weight along z x value of a channel) x (weight along y x
+// weight along x), so the contributions of one sample per patch to the whole box are one outer
+// product, v_mfma_f32_16x16x1_4b_f32: operand A holds (z, channel) in its 16 rows, B holds (y, x)
+// in its 16 columns, and the four blocks of the instruction are the four patches.  Sixteen of them add
+// a whole step of the wave with no memory access, no fold and no conflict.  Result register
+// 4b + v of lane l is channel v of voxel (x, y, z) = (l & 3, l >> 2 & 3, l >> 4) of patch b, a float4
+// of one voxel per lane, so a box goes to the LDS window in one conflict-free
+// read-modify-write when the patch's samples leave it.
 struct Brick4 {
     Window win;
-    int cmask;            // corner-order mirror of the camera (corner_mask)
-    volatile lds_f4* s;   // [kB3]
-    volatile lds_u8* tag; // [kB3] lane ids
+    volatile lds_f4* s;  // [kB3]
+    lds_float* stage;    // [4][kStageRow] the values of a step, one float4 per lane
+    f16v acc;            // sums of the four boxes
+    float fb[3];         // low corner of the own patch's box
+    bool up[3];          // the march goes towards +axis (wave-uniform)
+    bool placed;         // the window has a place
+    int sb[4][3];        // low corners of the four boxes (wave-uniform)
+    unsigned live;       // bit q: box q holds sums (wave-uniform)
 
-    __device__ __forceinline__ void init(f4* sb, unsigned char* tb) {
-        s = (volatile lds_f4*)sb;
-        tag = (volatile lds_u8*)tb;
+    __device__ __forceinline__ void init(f4* sb4, float* st) {
+        s = (volatile lds_f4*)sb4;
+        stage = (lds_float*)st;
         win.o[0] = win.o[1] = win.o[2] = -(1 << 24);
+        placed = false;
         for (int i = lane_id(); i < kB3; i += 64) s[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    // Flush one leaving voxel per lane (a uniform call: every lane holds one).  Where most voxels
-    // of the pass carry all four channels (a medium with some density everywhere), the adds go
-    // out four lanes per voxel, one channel each, so a voxel's four adds form one 16-byte run and
-    // the L2 sees about a quarter of the atomic requests; where most carry only the sigma channel
-    // (empty space: alpha = 0 zeroes the colour channels), each lane sends its own nonzero channels.
-    template <class Sink>
-    __device__ __forceinline__ void flush_voxel(const Geo& G, int x, int y, int z, Sink& out) {
-        const int sl = ring_slot(x, y, z);
-        const f4 v = s[sl];
-        const bool in = x >= 0 && y >= 0 && z >= 0 && x < G.nx && y < G.ny && z < G.nz;
-        const int u = (z * G.ny + y) * G.nx + x;
-        const bool full = in && v.x != 0.0f && v.y != 0.0f && v.z != 0.0f && v.w != 0.0f;
-        if (__popcll(__ballot(full)) >= 32) {
-            const int ch = lane_id() & 3;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int j = g * 16 + (lane_id() >> 2);
-                const int uj = __shfl(u, j, 64);
-                const int slj = __shfl(sl, j, 64);
-                const int inj = __shfl(in ? 1 : 0, j, 64);
-                const float f = ((volatile lds_float*)s)[4 * slj + ch];
-                if (inj && f != 0.0f) out.one(uj, ch, f);
-            }
-        } else if (in && (v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f)) {
-            const float vv[4] = {v.x, v.y, v.z, v.w};
-            out(u, vv);
+        for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            fb[a] = -1e6f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sb[q][a] = 0;
         }
-        s[sl] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        live = 0u;
+    }
+    // The march direction of the wave's rays (back to front).
+    __device__ __forceinline__ void set_direction(const float gd[3]) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) up[a] = __builtin_amdgcn_readfirstlane(__float_as_int(gd[a])) < 0;
+    }
+    // Flush the window's plane at coordinate c of axis A: four rounds of 16 voxels, four lanes per
+    // voxel (one channel each), so a voxel's adds form one 16-byte run, a row's 128 bytes.
+    template <int A, class Sink>
+    __device__ __forceinline__ void flush_plane(const Geo& G, int c, Sink& out) {
+        const int n[3] = {G.nx, G.ny, G.nz};
+        if (c < 0 || c >= n[A]) return;  // outside the grid every weight is zero
+        constexpr int P = A == 0 ? 1 : 0, Q = A == 2 ? 1 : 2;
+        constexpr int kRing[3] = {4, 4 * kB, 4 * kB * kB};  // floats per ring step along an axis
+        const int pitch[3] = {1, G.nx, G.nx * G.ny};
+        const int l = lane_id(), ch = l & 3;
+        const int cp = win.o[P] + ((l >> 2) & (kB - 1));
+        const int sl = (c & (kB - 1)) * kRing[A] + (cp & (kB - 1)) * kRing[P] + ch;
+        const bool in = (unsigned)cp < (unsigned)n[P];
+        const int u = c * pitch[A] + cp * pitch[P];
+        volatile lds_float* f = (volatile lds_float*)s;
+        float v[4];
+        int at[4], cq[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            cq[g] = win.o[Q] + (l >> 5) + 2 * g;
+            at[g] = sl + (cq[g] & (kB - 1)) * kRing[Q];
+            v[g] = f[at[g]];
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f[at[g]] = 0.0f;
+            if (in && (unsigned)cq[g] < (unsigned)n[Q] && v[g] != 0.0f) out.one(u + cq[g] * pitch[Q], ch, v[g]);
+        }
+    }
+    template <int A, class Sink>
+    __device__ __forceinline__ void move_axis(const Geo& G, int no, Sink& out) {
+        const int d = no - win.o[A];
+        if (d == 0) return;
+        const int cnt = min(abs(d), kB);
+        int c = d > 0 ? win.o[A] : win.o[A] + kB - 1;
+#pragma unroll 1
+        for (int t = 0; t < cnt; ++t) {
+            flush_plane<A>(G, c, out);
+            c += d > 0 ? 1 : -1;
+        }
+        win.o[A] = no;
     }
     __device__ __forceinline__ void clear_head(int n) {
         for (int i = lane_id(); i < n; i += 64) s[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     }
+    // Add box Q to the window and clear it; voxels the window does not cover go to HBM.
+    template <int Q, class Sink>
+    __device__ __forceinline__ void flush_box(const Geo& G, Sink& out) {
+        const int l = lane_id();
+        const int x = sb[Q][0] + (l & 3), y = sb[Q][1] + ((l >> 2) & 3), z = sb[Q][2] + (l >> 4);
+        const f4 v = f4{acc[4 * Q], acc[4 * Q + 1], acc[4 * Q + 2], acc[4 * Q + 3]};
+        const bool in = (unsigned)(x - win.o[0]) < (unsigned)kB && (unsigned)(y - win.o[1]) < (unsigned)kB &&
+                        (unsigned)(z - win.o[2]) < (unsigned)kB;
+        if (in) {
+            const int sl = ring_slot(x, y, z);
+            s[sl] = s[sl] + v;
+        } else if ((v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f) && x >= 0 && y >= 0 && z >= 0 &&
+                   x < G.nx && y < G.ny && z < G.nz) {
+            const float vv[4] = {v.x, v.y, v.z, v.w};
+            out((z * G.ny + y) * G.nx + x, vv);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[4 * Q + i] = 0.0f;
+        live &= ~(1u << Q);
+    }
     template <class Sink>
-    __device__ __forceinline__ void fit(const Geo& G, bool on, const int lo[3], const int hi[3], Sink& out) {
-        auto fl = [&](int x, int y, int z) { flush_voxel(G, x, y, z, out); };
-        win.fit(on, lo, hi, fl);
+    __device__ __forceinline__ void flush_boxes(const Geo& G, unsigned which, Sink& out) {
+        if (which & 1u) flush_box<0>(G, out);
+        if (which & 2u) flush_box<1>(G, out);
+        if (which & 4u) flush_box<2>(G, out);
+        if (which & 8u) flush_box<3>(G, out);
+    }
+    // Move the window so that the boxes in `which` lie inside on the side the march goes to; boxes
+    // whose trailing side it would leave are added to it first.  Returns the boxes still to flush.
+    template <class Sink>
+    __device__ __forceinline__ unsigned follow(const Geo& G, unsigned which, Sink& out) {
+        int no[3] = {win.o[0], win.o[1], win.o[2]};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (which & (1u << q)) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    if (!placed) no[a] = up[a] ? sb[q][a] : sb[q][a] + 4 - kB;
+                    else if (up[a]) no[a] = max(no[a], sb[q][a] + 4 - kB);
+                    else no[a] = min(no[a], sb[q][a]);
+                }
+                placed = true;
+            }
+        if (no[0] == win.o[0] && no[1] == win.o[1] && no[2] == win.o[2]) return which;
+        unsigned behind = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) behind |= (up[a] ? sb[q][a] < no[a] : sb[q][a] + 4 > no[a] + kB) ? 1u << q : 0u;
+        behind &= live;
+        flush_boxes(G, behind, out);
+        move_axis<0>(G, no[0], out);
+        move_axis<1>(G, no[1], out);
+        move_axis<2>(G, no[2], out);
+        return which & ~behind;
     }
     template <class Sink>
     __device__ __forceinline__ void flush_all(const Geo& G, Sink& out) {
-        auto fl = [&](int x, int y, int z) { flush_voxel(G, x, y, z, out); };
-        win.each_voxel(fl);
+        const unsigned left = follow(G, live, out);
+        flush_boxes(G, left, out);
+#pragma unroll 1
+        for (int t = 0; t < kB; ++t) flush_plane<2>(G, win.o[2] + t, out);
     }
-    // add val * weight(corner) to the 8 corners of every lane that is on (uniform call).
-    // Lanes of one grid cell share all eight corners.  Before the election, the lanes of a
-    // 2x2 quad that sit in one cell fold their contributions into one lane (quad_folds, DPP
-    // lane swaps), so one lane per group enters the election.  Lanes of different cells
-    // never target one voxel with the same corner index, so every lane of a 2x2 lane quad
-    // visits the corners in the same order, rotated per quad (and mirrored per camera,
-    // corner_mask) so that neighbouring quads update different voxels in the same round.
+    // Place the boxes of the patches in `rows` (bit q) at the trailing side of their samples (lanes
+    // with want set, clamped grid coordinates g), so that room is left ahead of the march.  A box covers
+    // coordinates [fb, fb + 3].
     template <class Sink>
-    __device__ __forceinline__ void scatter8(const Geo& G, bool on, bool inb, const Corners& c, f4 val, bool two,
-                                             f4 val2, const float f2[3], Sink& out) {
-        // two: a second sample of the same cell (fractional position f2) is added with this one
-        const float v2x0 = 1.0f - f2[0], v2y0 = 1.0f - f2[1], v2z0 = 1.0f - f2[2];
-        auto w2_of = [&](int i) {
-            return two ? ((i & 1) ? f2[0] : v2x0) * ((i & 2) ? f2[1] : v2y0) * ((i & 4) ? f2[2] : v2z0) : 0.0f;
-        };
-        if (wave_any(on && !inb)) {  // corners outside the window: straight to HBM
-            if (on && !inb) {
+    __device__ __forceinline__ void rebase(const Geo& G, unsigned rows, bool want, const float g[3], Sink& out) {
+        const unsigned full = rows & live;
+        if (full) {
+            const unsigned left = follow(G, full, out);
+            flush_boxes(G, left, out);
+        }
+        const bool mine = (rows >> (lane_id() >> 4)) & 1u;
 #pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float nb;
+            if (up[a]) {
+                float m = want ? g[a] : 1e9f;
+                m = fminf(m, dpp_ror<8>(m));
+                m = fminf(m, dpp_ror<4>(m));
+                m = fminf(m, dpp_ror<2>(m));
+                m = fminf(m, dpp_ror<1>(m));
+                nb = floorf(m);
+            } else {
+                float m = want ? g[a] : -1e9f;
+                m = fmaxf(m, dpp_ror<8>(m));
+                m = fmaxf(m, dpp_ror<4>(m));
+                m = fmaxf(m, dpp_ror<2>(m));
+                m = fmaxf(m, dpp_ror<1>(m));
+                nb = ceilf(m) - 3.0f;
+            }
+            fb[a] = mine ? nb : fb[a];
+            const int ib = (int)fb[a];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sb[q][a] = __builtin_amdgcn_readlane(ib, 16 * q);
+        }
+    }
+    template <int K>
+    __device__ __forceinline__ void outer(const float rg[3], const float at[3], const float vals[16]) {
+        const float wx = tent(dpp_bcast<K>(rg[0]) - at[0]);
+        const float wy = tent(dpp_bcast<K>(rg[1]) - at[1]);
+        const float wz = tent(dpp_bcast<K>(rg[2]) - at[2]);
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(wz * vals[K], wy * wx, acc, 0, 0, 0);
+    }
+    // Add val * weight(corner) to the 8 corners of every lane that is on (uniform call).
+    template <class Sink>
+    __device__ __forceinline__ void scatter(const Geo& G, bool on, const Corners& c, f4 val, Sink& out) {
+        // a value that is not finite stays out of the outer products (0 * inf would spread it over the box)
+        const bool want = on && fabsf(val.x) + fabsf(val.y) + fabsf(val.z) + fabsf(val.w) < INFINITY;
+        float rg[3] = {c.g[0] - fb[0], c.g[1] - fb[1], c.g[2] - fb[2]};
+        bool fits = want && in_box(rg);
+        const unsigned long long miss = __ballot(want && !fits);
+        if (miss) {
+            rebase(G, rows_of(miss), want, c.g, out);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) rg[a] = c.g[a] - fb[a];
+            fits = want && in_box(rg);
+        }
+        if (wave_any(on && !fits)) {  // samples their patch's box cannot take
+            if (on && !fits) {
+                const int hi[3] = {c.i[0] + 1, c.i[1] + 1, c.i[2] + 1};
+                const bool inb = win.inside(c.i, hi);
+#pragma unroll 1
                 for (int i = 0; i < 8; ++i) {
                     const int x = c.i[0] + (i & 1), y = c.i[1] + ((i >> 1) & 1), z = c.i[2] + (i >> 2);
-                    const f4 add = val * c.w[i] + val2 * w2_of(i);
-                    const float vv[4] = {add.x, add.y, add.z, add.w};
-                    out((z * G.ny + y) * G.nx + x, vv);
-                }
-            }
-        }
-        const bool mine = on && inb;
-        if (!wave_any(mine)) return;
-        const int lane = lane_id();
-        const unsigned char tag_id = (unsigned char)lane;
-        // The swaps run in straight-line code with every lane active: a lane swap executed
-        // under a partial mask would read the other lane's register as it was last written.
-        const QuadFolds q = quad_folds(mine, c.v);
-        const int phi = ((((lane & 7) >> 1) << 1) + (lane >> 4)) & 7;
-        const int sx0 = c.i[0] & 7, sx1 = (c.i[0] + 1) & 7;
-        const int sy0 = (c.i[1] & 7) << 3, sy1 = ((c.i[1] + 1) & 7) << 3;
-        const int sz0 = (c.i[2] & 7) << 6, sz1 = ((c.i[2] + 1) & 7) << 6;
-        const float wx0 = 1.0f - c.f[0], wy0 = 1.0f - c.f[1], wz0 = 1.0f - c.f[2];
-        // the next corner's slot and value are formed while this corner's first round waits on LDS
-        auto corner = [&](int r, int& sl, f4& add) {
-            const int i = ((r + phi) & 7) ^ cmask;
-            const bool bx = i & 1, by = i & 2, bz = i & 4;
-            sl = (bz ? sz1 : sz0) + (by ? sy1 : sy0) + (bx ? sx1 : sx0);
-            const float w = mine ? (bx ? c.f[0] : wx0) * (by ? c.f[1] : wy0) * (bz ? c.f[2] : wz0) : 0.0f;
-            const float w2 = mine ? w2_of(i) : 0.0f;
-            const f4 a0 = val * w + val2 * w2;
-            {
-#pragma clang fp contract(off)
-                add = a0;
-                // a donor hands its value over; every other lane hands over zero
-                const f4 zero = f4{0.0f, 0.0f, 0.0f, 0.0f};
-                add += dpp_xor1(q.give_x ? add : zero);
-                add += dpp_row_xor8(q.give_y ? add : zero);
-                add += dpp_row_xor8(dpp_xor1(q.give_d ? add : zero));
-            }
-        };
-        int sl;
-        f4 add;
-        corner(0, sl, add);
-#pragma unroll 1
-        for (int r = 0; r < 8; ++r) {
-            bool pend = q.keep;
-            unsigned char t = 0;
-            f4 cur = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (pend) {
-                tag[sl] = tag_id;
-                t = tag[sl];
-                cur = s[sl];
-            }
-            int sl_n = 0;
-            f4 add_n = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (r < 7) corner(r + 1, sl_n, add_n);
-            if (pend && t == tag_id) {
-                s[sl] = cur + add;
-                pend = false;
-            }
-            while (wave_any(pend)) {
-                if (pend) {
-                    tag[sl] = tag_id;
-                    // read the slot with the tag, so a round waits on LDS once
-                    const unsigned char t2 = tag[sl];
-                    const f4 c2 = s[sl];
-                    if (t2 == tag_id) {
-                        s[sl] = c2 + add;
-                        pend = false;
+                    const float w = ((i & 1) ? c.f[0] : 1.0f - c.f[0]) * ((i & 2) ? c.f[1] : 1.0f - c.f[1]) *
+                                    ((i & 4) ? c.f[2] : 1.0f - c.f[2]);
+                    const f4 add = val * w;
+                    if (inb) {
+                        lds_float* p = (lds_float*)(s + ring_slot(x, y, z));
+                        lds_add(p, add.x);
+                        lds_add(p + 1, add.y);
+                        lds_add(p + 2, add.z);
+                        lds_add(p + 3, add.w);
+                    } else {
+                        const float vv[4] = {add.x, add.y, add.z, add.w};
+                        out((z * G.ny + y) * G.nx + x, vv);
                     }
                 }
             }
-            sl = sl_n;
-            add = add_n;
         }
+        const unsigned long long some = __ballot(fits);
+        if (!some) return;
+        live |= rows_of(some);
+        const int l = lane_id();
+        const f4 zero = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        *(lds_f4*)(stage + (l >> 4) * kStageRow + (l & 15) * 4) = fits ? val : zero;
+        wave_fence();
+        const lds_float* from = stage + (l >> 4) * kStageRow + (l & 3);
+        float vals[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) vals[k] = from[4 * k];
+        wave_fence();
+        const float at[3] = {(float)(l & 3), (float)((l >> 2) & 3), (float)((l >> 2) & 3)};
+        outer<0>(rg, at, vals); outer<1>(rg, at, vals); outer<2>(rg, at, vals); outer<3>(rg, at, vals);
+        outer<4>(rg, at, vals); outer<5>(rg, at, vals); outer<6>(rg, at, vals); outer<7>(rg, at, vals);
+        outer<8>(rg, at, vals); outer<9>(rg, at, vals); outer<10>(rg, at, vals); outer<11>(rg, at, vals);
+        outer<12>(rg, at, vals); outer<13>(rg, at, vals); outer<14>(rg, at, vals); outer<15>(rg, at, vals);
+    }
+    // bit q: the ballot has a lane of row q
+    static __device__ __forceinline__ unsigned rows_of(unsigned long long b) {
+        const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+        return ((lo & 0xffffu) ? 1u : 0u) | ((lo >> 16) ? 2u : 0u) | ((hi & 0xffffu) ? 4u : 0u) | ((hi >> 16) ? 8u : 0u);
+    }
+    static __device__ __forceinline__ float tent(float d) {
+        return __builtin_amdgcn_fmed3f(1.0f - fabsf(d), 0.0f, 1.0f);
+    }
+    static __device__ __forceinline__ bool in_box(const float rg[3]) {
+        return fmaxf(fmaxf(fabsf(rg[0] - 1.5f), fabsf(rg[1] - 1.5f)), fabsf(rg[2] - 1.5f)) <= 1.5f;
     }
 };
 
@@ -698,7 +795,10 @@ struct SinkY {  // y[4u + c], c < 4
         for (int c = 0; c < 4; ++c)
             if (v[c] != 0.0f) atomic_add(p + c, v[c]);
     }
-    __device__ __forceinline__ void one(int u, int c, float v) const { atomic_add(y + 4 * (size_t)u + c, v); }
+    // (a 32-bit byte offset: the parameters take less than 4 GiB)
+    __device__ __forceinline__ void one(int u, int c, float v) const {
+        atomic_add((float*)((char*)y + (16u * (unsigned)u + 4u * (unsigned)c)), v);
+    }
 };
 struct SinkGrad {  // grad[4u + c] (c < 4) and blocks[5u + c] (channels 4..8)
     float* grad;
@@ -963,30 +1063,18 @@ __device__ __forceinline__ void adjoint_scatter(const Geo& G, const Ray& r, bool
     const float t_max = wave_max_f(r.K > 0 ? r.tf : -INFINITY);
     const int off = r.K > 0 ? (int)((t_max - r.tf) / unit + 0.5f) : 0;
     const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
-    // A lane whose next sample lies in the same cell hands this sample's value to the next
-    // step, which scatters both together (one deferred sample at most): fewer updates enter
-    // the elections.
-    bool dpend = false;
-    f4 dval = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    float df[3] = {0.0f, 0.0f, 0.0f};
+    B.set_direction(r.gd);
     for (int j = 0; j < J; ++j) {
         const int m = j - off;
         const bool on = m >= 0 && m < r.K;
         const int k = r.K - 1 - m;
         Corners c{};
         float dk = 0.0f;
-        int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
         if (on) {
             float g[3];
             dk = sample_at(G, r, k, g);
             corners(G, g, c);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                lo[a] = c.i[a];
-                hi[a] = c.i[a] + 1;
-            }
         }
-        B.fit(G, on, lo, hi, sink);
         f4 val = {0.0f, 0.0f, 0.0f, 0.0f};
         if (on) {
             float sg, c0, c1, c2;
@@ -1002,21 +1090,7 @@ __device__ __forceinline__ void adjoint_scatter(const Geo& G, const Ray& r, bool
             Tn = T;
             val = f4{A * u[0], A * u[1], A * u[2], ds};
         }
-        bool defer = false;
-        if (on && !dpend && k > 0) {
-            float gn[3];
-            (void)sample_at(G, r, k - 1, gn);
-            defer = cell_key(G, gn) == c.v;
-        }
-        const bool two = on && dpend;
-        B.scatter8(G, on && !defer, on && !defer && B.win.inside(lo, hi), c, val, two, dval, df, sink);
-        if (defer) {
-            dval = val;
-            df[0] = c.f[0];
-            df[1] = c.f[1];
-            df[2] = c.f[2];
-        }
-        dpend = defer;
+        B.scatter(G, on, c, val, sink);
     }
     B.flush_all(G, sink);
 }
@@ -1262,7 +1336,9 @@ struct Pix {
     long long ray;
 };
 
-// Workgroup b covers a 16x8 pixel tile of camera b / n_tiles; wave w its 8x8 half w.
+// Workgroup b covers a 16x8 pixel tile of camera b / n_tiles; wave w its 8x8 half w.  With
+// PATCH each row of 16 lanes holds a 4x4 patch of it, else two lines of 8 pixels.
+template <bool PATCH>
 __device__ __forceinline__ Pix pixel_of(const Geo& G) {
     Pix p;
     const int b = blockIdx.x;
@@ -1270,8 +1346,10 @@ __device__ __forceinline__ Pix pixel_of(const Geo& G) {
     const int tile = b - p.cam * G.n_tiles;
     const int ty = tile / G.tiles_x, tx = tile - ty * G.tiles_x;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    p.px = tx * kTileX + wave * 8 + (lane & 7);
-    p.py = ty * kTileY + (lane >> 3);
+    const int lx = PATCH ? ((lane >> 4) & 1) * 4 + (lane & 3) : lane & 7;
+    const int ly = PATCH ? (lane >> 5) * 4 + ((lane >> 2) & 3) : lane >> 3;
+    p.px = tx * kTileX + wave * 8 + lx;
+    p.py = ty * kTileY + ly;
     p.active = p.px < G.width && p.py < G.height;
     p.ray = ((long long)p.cam * G.height + p.py) * G.width + p.px;
     return p;
@@ -1281,18 +1359,19 @@ template <int MODE>
 struct Lds {
     static constexpr int NCH = MODE == M_GRAD ? 9 : 4;
     static constexpr bool SCATTER = MODE == M_VJP || MODE == M_JTJ || MODE == M_GRAD;
+    static constexpr int WAVES = (MODE == M_VJP || MODE == M_JTJ) ? 4 : 1;  // waves per SIMD to leave registers for
 };
 
 template <int MODE, int PD>
-__global__ __launch_bounds__(kBlock) void k_ray(Geo G, RayArgs A) {
+__global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs A) {
     constexpr int NCH = Lds<MODE>::NCH;
     constexpr bool SCATTER = Lds<MODE>::SCATTER;
     constexpr bool JT = MODE == M_VJP || MODE == M_JTJ;
     __shared__ f4 s_brick[(SCATTER && !JT) ? kWaves * NCH * kB3 / 4 : 1];
     __shared__ f4 s_brick4[JT ? kWaves * kB3 : 1];
-    __shared__ unsigned char s_tag[(SCATTER && MODE != M_GRAD) ? kWaves * kB3 : 1];
+    __shared__ f4 s_stage[JT ? kWaves * kStageRow : 1];
     if (A.done && *A.done) return;
-    const Pix p = pixel_of(G);
+    const Pix p = pixel_of<JT>(G);
     const int wave = threadIdx.x >> 6;
     const int units = G.nvox + G.n_layers * G.env_w * G.env_h;
     XL<PD> X;
@@ -1352,8 +1431,7 @@ __global__ __launch_bounds__(kBlock) void k_ray(Geo G, RayArgs A) {
         TexTable<NCH> TT;
         if constexpr (JT) {
             Brick4 B;
-            B.init(s_brick4 + wave * kB3, s_tag + wave * kB3);
-            B.cmask = corner_mask(A.cams[p.cam]);
+            B.init(s_brick4 + wave * kB3, (float*)(s_stage + wave * kStageRow));
             TT.init((int*)(s_brick4 + wave * kB3), (float*)(s_brick4 + wave * kB3 + 16));
             float u[3] = {0.0f, 0.0f, 0.0f};
             float u4 = 0.0f;
@@ -1403,7 +1481,7 @@ __global__ __launch_bounds__(kBlock) void k_ray(Geo G, RayArgs A) {
 // already corners of the previous sample (per-axis sets of one or two indices).
 __global__ __launch_bounds__(kBlock) void k_footprint(Geo G, const DevCam* cams, int32_t* per_ray,
                                                       unsigned long long* totals) {
-    const Pix p = pixel_of(G);
+    const Pix p = pixel_of<false>(G);
     unsigned long long U = 0, nl = 0, hit = 0;
     if (p.active) {
         Ray r;
