@@ -51,6 +51,10 @@ struct VecF4 {  // FP32 float4 per unit
                            __int_as_float((int)q[3]));
     }
     __device__ __forceinline__ float4 operator()(int i) const { return load(i * kBytes, 0); }
+    // a unit as it is stored, and its values
+    typedef float4 Raw;
+    __device__ __forceinline__ Raw raw(int i) const { return load(i * kBytes, 0); }
+    static __device__ __forceinline__ float4 value(Raw q) { return q; }
 };
 
 template <int PD>
@@ -61,12 +65,17 @@ template <>
 struct XL<PERF_BF16> {  // bfloat16 x 4 per unit
     __amdgpu_buffer_rsrc_t r;
     static constexpr int kBytes = 8;
-    __device__ __forceinline__ float4 load(int voff, int soff) const {
-        const auto q = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
-        const unsigned a = (unsigned)q[0], b = (unsigned)q[1];
-        return make_float4(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u), __uint_as_float(b << 16),
-                           __uint_as_float(b & 0xffff0000u));
+    typedef uint2 Raw;
+    static __device__ __forceinline__ float4 value(Raw q) {
+        return make_float4(__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u), __uint_as_float(q.y << 16),
+                           __uint_as_float(q.y & 0xffff0000u));
     }
+    __device__ __forceinline__ Raw raw_at(int voff, int soff) const {
+        const auto q = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+        return make_uint2((unsigned)q[0], (unsigned)q[1]);
+    }
+    __device__ __forceinline__ Raw raw(int i) const { return raw_at(i * kBytes, 0); }
+    __device__ __forceinline__ float4 load(int voff, int soff) const { return value(raw_at(voff, soff)); }
     __device__ __forceinline__ float4 operator()(int i) const { return load(i * kBytes, 0); }
 };
 
@@ -860,6 +869,46 @@ __device__ __forceinline__ float4 gather4(const L& X, const Corners& c, const Co
     return s;
 }
 
+// The corners of a lane's cell held in registers from sample to sample.  Slot b holds the corner
+// whose coordinate parities are the bits of b, so a corner that two consecutive cells share stays
+// in its slot and only the others are loaded.
+struct CellWin {
+    int o[3][2];  // unit offset along each axis of the even and of the odd coordinate
+    unsigned long long ch[3][2];  // lanes whose even / odd coordinate along an axis changed
+    float w[8];   // weights per slot
+
+    __device__ __forceinline__ void init() {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) o[a][0] = o[a][1] = -1;
+    }
+    __device__ __forceinline__ void move(const Geo& G, const float g[3]) {
+        const int n[3] = {G.nx, G.ny, G.nz};
+        const int pitch[3] = {1, G.nx, G.nx * G.ny};
+        float gw[3][2];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float gc = fminf(fmaxf(g[a], 0.0f), (float)(n[a] - 1));
+            const int i = min((int)gc, n[a] - 2);
+            const float f = gc - (float)i;
+            const bool odd = i & 1;
+            const int lo = i * pitch[a], hi = lo + pitch[a];
+            const int e = odd ? hi : lo, d = odd ? lo : hi;
+            ch[a][0] = __ballot(e != o[a][0]);
+            ch[a][1] = __ballot(d != o[a][1]);
+            o[a][0] = e;
+            o[a][1] = d;
+            gw[a][0] = odd ? f : 1.0f - f;
+            gw[a][1] = odd ? 1.0f - f : f;
+        }
+#pragma unroll
+        for (int b = 0; b < 8; ++b) w[b] = gw[0][b & 1] * (gw[1][(b >> 1) & 1] * gw[2][b >> 2]);
+    }
+    __device__ __forceinline__ bool changed(int b) const {
+        return __builtin_amdgcn_inverse_ballot_w64(ch[0][b & 1] | ch[1][(b >> 1) & 1] | ch[2][b >> 2]);
+    }
+    __device__ __forceinline__ int unit(int b) const { return o[0][b & 1] + (o[1][(b >> 1) & 1] + o[2][b >> 2]); }
+};
+
 // Gather the trilinear sample of (c, sigma) at corners c.
 template <int PD>
 __device__ __forceinline__ void gather(XL<PD> X, const Corners& c, int nx, int nxy, float& sg, float& c0, float& c1,
@@ -884,28 +933,50 @@ __device__ __forceinline__ void forward(const Geo& G, const Ray& r, bool live, X
     depth.c = 0.0f;
     H[0] = H[1] = H[2] = 0.0f;
     Hd[0] = Hd[1] = Hd[2] = 0.0f;
-    const int nx = G.nx, nxy = G.nx * G.ny;
     const float unit = G.h * G.step;
     const float t_min = wave_min_f(r.K > 0 ? r.tn : INFINITY);
     const int off = r.K > 0 ? (int)((r.tn - t_min) / unit + 0.5f) : 0;
     const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
+    CellWin cw;
+    cw.init();
+    typename XL<PD>::Raw qx[8];
+    float4 qv[TAN ? 8 : 1];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) qx[b] = typename XL<PD>::Raw{};
+    if constexpr (TAN) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) qv[b] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
     for (int j = 0; j < J; ++j) {
         const int k = j - off;
         if (k < 0 || k >= r.K) continue;
         float g[3];
         const float dk = sample_at(G, r, k, g);
-        Corners c;
-        corners(G, g, c);
-        float sg, c0, c1, c2;
-        gather<PD>(X, c, nx, nxy, sg, c0, c1, c2);
-        float sgd = 0.0f, cd0 = 0.0f, cd1 = 0.0f, cd2 = 0.0f;
-        if constexpr (TAN) {
-            const float4 t = gather4(V, c, corner_offs<VecF4::kBytes>(nx, nxy));
-            cd0 = t.x;
-            cd1 = t.y;
-            cd2 = t.z;
-            sgd = t.w;
+        cw.move(G, g);
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+            if (cw.changed(b)) {
+                const int u = cw.unit(b);
+                qx[b] = X.raw(u);
+                if constexpr (TAN) qv[b] = V(u);
+            }
+        float4 sx = make_float4(0.0f, 0.0f, 0.0f, 0.0f), sv = sx;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const float4 q = XL<PD>::value(qx[b]);
+            sx.x += cw.w[b] * q.x;
+            sx.y += cw.w[b] * q.y;
+            sx.z += cw.w[b] * q.z;
+            sx.w += cw.w[b] * q.w;
+            if constexpr (TAN) {
+                sv.x += cw.w[b] * qv[b].x;
+                sv.y += cw.w[b] * qv[b].y;
+                sv.z += cw.w[b] * qv[b].z;
+                sv.w += cw.w[b] * qv[b].w;
+            }
         }
+        const float c0 = sx.x, c1 = sx.y, c2 = sx.z, sg = sx.w;
+        const float cd0 = sv.x, cd1 = sv.y, cd2 = sv.z, sgd = sv.w;
         const float tau = sg * dk;
         depth.add(tau);
         const float e = exp_neg(tau);
