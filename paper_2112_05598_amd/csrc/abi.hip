@@ -20,7 +20,7 @@ struct perf_scene {
     const float* targets;
     hipStream_t stream;
     int64_t n_rays, units, P;
-    int n_ray_blocks;
+    int64_t n_render_blocks, n_grad_blocks;  // workgroups (partial sums of F) of the render and gradient passes
     DevCam* cams;
     double* partials;
     double* scalars;
@@ -132,8 +132,7 @@ Layout make_layout(const perf_scene_desc& d, int n_cams) {
     const int64_t units = (int64_t)d.nx * d.ny * d.nz + (int64_t)d.n_layers * d.env_w * d.env_h;
     const int64_t P = 4 * units;
     const Geo g = make_geo(d, n_cams);
-    const int64_t ray_blocks = (int64_t)n_cams * g.n_tiles;
-    L.n_partials = ray_blocks > 2 * kVecGrid ? ray_blocks : 2 * kVecGrid;
+    L.n_partials = std::max<int64_t>(2 * kVecGrid, std::max(ray_blocks(g, false), split_rays(M_RENDER, g) ? ray_blocks(g, true) : 0));
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -213,7 +212,8 @@ int32_t perf_init_scene(const perf_scene_desc* desc, const perf_camera* cams, in
     s->units = (int64_t)desc->nx * desc->ny * desc->nz + (int64_t)desc->n_layers * desc->env_w * desc->env_h;
     s->P = 4 * s->units;
     s->n_rays = (int64_t)n_cams * desc->width * desc->height;
-    s->n_ray_blocks = n_cams * s->geo.n_tiles;
+    s->n_render_blocks = ray_blocks(s->geo, split_rays(M_RENDER, s->geo));
+    s->n_grad_blocks = ray_blocks(s->geo, split_rays(M_GRAD, s->geo));
     s->cams = (DevCam*)(s->ws + L.cams);
     s->partials = (double*)(s->ws + L.partials);
     s->scalars = (double*)(s->ws + L.scalars);
@@ -293,7 +293,7 @@ int32_t perf_render_residuals(perf_scene* s, const void* d_x, float* d_r, double
     a.partials = d_F ? s->partials : nullptr;
     a.thresh = s->desc.render_threshold;
     CK(launch_ray(M_RENDER, s->desc.param_dtype, s->geo, a, s->stream));
-    if (d_F) CK(launch_sum_partials(s->partials, s->n_ray_blocks, 0.5, d_F, s->stream));
+    if (d_F) CK(launch_sum_partials(s->partials, s->n_render_blocks, 0.5, d_F, s->stream));
     return PERF_OK;
 }
 
@@ -339,7 +339,7 @@ static int32_t grad_pass(perf_scene* s, const void* xg, float* grad, float* bloc
     a.blocks = blocks;
     a.partials = s->partials;
     CK(launch_ray(M_GRAD, s->desc.param_dtype, s->geo, a, s->stream));
-    if (want_F) CK(launch_sum_partials(s->partials, s->n_ray_blocks, 0.5, s->scalars + S_F, s->stream));
+    if (want_F) CK(launch_sum_partials(s->partials, s->n_grad_blocks, 0.5, s->scalars + S_F, s->stream));
     return PERF_OK;
 }
 
@@ -421,7 +421,7 @@ static int32_t trial_objective(perf_scene* s, const float* d_x, const float* d_d
     a.targets = s->targets;
     a.partials = s->partials;
     CK(launch_ray(M_RENDER, s->desc.param_dtype, s->geo, a, s->stream));
-    CK(launch_sum_partials(s->partials, s->n_ray_blocks, 0.5, s->scalars + S_TMP, s->stream));
+    CK(launch_sum_partials(s->partials, s->n_render_blocks, 0.5, s->scalars + S_TMP, s->stream));
     return PERF_OK;
 }
 

@@ -89,6 +89,10 @@ struct RayArgs {
     float thresh;            // RENDER: volume counts as transparent when 1 - T_exit < thresh (0 = off)
 };
 
+// workgroups of a ray launch (one partial each): a whole tile per workgroup, or a quarter of it with
+// four lanes per ray (split_rays: the rule launch_ray goes by)
+int64_t ray_blocks(const Geo& g, bool split);
+bool split_rays(int mode, const Geo& g);
 hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st);
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,
                             hipStream_t st);

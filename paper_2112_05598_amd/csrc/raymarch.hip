@@ -630,10 +630,12 @@ struct Brick4 {
     }
     template <int K>
     __device__ __forceinline__ void outer(const float rg[3], const float at[3], const float vals[16]) {
-        const float wx = tent(dpp_bcast<K>(rg[0]) - at[0]);
+        const float dx = fabsf(dpp_bcast<K>(rg[0]) - at[0]);
         const float wy = tent(dpp_bcast<K>(rg[1]) - at[1]);
         const float wz = tent(dpp_bcast<K>(rg[2]) - at[2]);
-        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(wz * vals[K], wy * wx, acc, 0, 0, 0);
+        // wy (1 - dx), not below 0
+        const float wxy = __builtin_amdgcn_fmed3f(fmaf(-dx, wy, wy), 0.0f, 1.0f);
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(wz * vals[K], wxy, acc, 0, 0, 0);
     }
     // Add val * weight(corner) to the 8 corners of every lane that is on (uniform call).
     template <class Sink>
@@ -1166,6 +1168,250 @@ __device__ __forceinline__ void adjoint_scatter(const Geo& G, const Ray& r, bool
     B.flush_all(G, sink);
 }
 
+// ------------------------------------------------------------------ four lanes per ray
+// The same marches with four lanes per ray: a wave covers 4x4 pixels, row q of 16 lanes a 2x2
+// quad of them, and lanes i, i + 4, i + 8, i + 12 of the row (slots 0 .. 3) take four consecutive
+// samples of a ray at a time.  The optical depth in front of a sample, its tangent and the
+// radiance behind it are sums along the ray, so they are scanned over the slots.  Four times as
+// many waves march a quarter of the steps.
+// (The lane swaps run with every lane active: they read the partner's register.)
+__device__ __forceinline__ int slot_id() { return (lane_id() >> 2) & 3; }
+// the value N slots in front, 0 in the first N slots
+template <int N>
+__device__ __forceinline__ float slot_shift(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x110 + 4 * N, 0xF, 0xF, true));
+}
+// inclusive sums over the slots, the total in every slot, and the value of slot s in every slot
+__device__ __forceinline__ float slot_scan(float v) {
+    v += slot_shift<1>(v);
+    return v + slot_shift<2>(v);
+}
+__device__ __forceinline__ float slot_sum(float v) {
+    v += dpp_ror<8>(v);
+    return v + dpp_ror<4>(v);
+}
+__device__ __forceinline__ float slot_bcast(float v, int t, int s) { return slot_sum(t == s ? v : 0.0f); }
+
+// A layer's bilinear lookup; zero where the ray does not hit it.
+template <int PD>
+__device__ __forceinline__ bool env_value(const Geo& G, const Ray& r, int l, bool live, XL<PD> X, Tex& tx, float& al,
+                                          float c[3]) {
+    al = c[0] = c[1] = c[2] = 0.0f;
+    if (!live || l >= G.n_layers || !env_hit(G, r, l, r.hit ? r.tf : 0.0f, tx)) return false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float4 q = X(tx.t[j]);
+        c[0] += tx.w[j] * q.x;
+        c[1] += tx.w[j] * q.y;
+        c[2] += tx.w[j] * q.z;
+        al += tx.w[j] * q.w;
+    }
+    return true;
+}
+
+template <int PD, bool TAN>
+__device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, XL<PD> X, VecF4 V, float H[3],
+                                         float& Texit, float& Tdexit, float Hd[3], Depth& depth, float thresh) {
+    const int t = slot_id();
+    depth.s = 0.0f;
+    depth.c = 0.0f;
+    H[0] = H[1] = H[2] = 0.0f;
+    Hd[0] = Hd[1] = Hd[2] = 0.0f;
+    float Vd = 0.0f;  // tangent of the optical depth
+    const int nx = G.nx, nxy = G.nx * G.ny;
+    const float unit = G.h * G.step;
+    const float t_min = wave_min_f(r.K > 0 ? r.tn : INFINITY);
+    const int off = r.K > 0 ? (int)((r.tn - t_min) / unit + 0.5f) : 0;
+    const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
+    for (int j = 0; j < J; j += 4) {
+        const int k = j + t - off;
+        const bool on = k >= 0 && k < r.K;
+        float tau = 0.0f, taud = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, cd0 = 0.0f, cd1 = 0.0f, cd2 = 0.0f;
+        if (on) {
+            float g[3], sg;
+            const float dk = sample_at(G, r, k, g);
+            Corners c;
+            corners(G, g, c);
+            if constexpr (TAN) {
+                const float4 q = gather4(V, c, corner_offs<VecF4::kBytes>(nx, nxy));
+                cd0 = q.x;
+                cd1 = q.y;
+                cd2 = q.z;
+                taud = q.w * dk;
+            }
+            gather<PD>(X, c, nx, nxy, sg, c0, c1, c2);
+            tau = sg * dk;
+        }
+        const float incl = slot_scan(tau);
+        const float T = exp_neg(depth.value() + slot_shift<1>(incl));
+        depth.add(slot_sum(tau));
+        const float e = exp_neg(tau);
+        const float al = one_minus_exp_neg(tau, e);
+        const float Ta = T * al;
+        H[0] += Ta * c0;
+        H[1] += Ta * c1;
+        H[2] += Ta * c2;
+        if constexpr (TAN) {
+            const float incd = slot_scan(taud);
+            // d T_k = -T_k d V_k, d alpha = e d tau
+            const float k1 = T * (e * taud - (Vd + slot_shift<1>(incd)) * al);
+            Vd += slot_sum(taud);
+            Hd[0] += k1 * c0 + Ta * cd0;
+            Hd[1] += k1 * c1 + Ta * cd1;
+            Hd[2] += k1 * c2 + Ta * cd2;
+        }
+    }
+    Texit = exp_neg(depth.value());
+    Tdexit = -Texit * Vd;
+    float T = Texit, Td = Tdexit;
+    if (thresh > 0.0f && 1.0f - T < thresh) {
+        // rendering rule (Sec. IV): a volume this transparent counts as empty
+        H[0] = H[1] = H[2] = 0.0f;
+        T = 1.0f;
+    }
+    // layers l0 .. l0 + 3, one per lane of the quad
+    for (int l0 = 0; l0 < G.n_layers; l0 += 4) {
+        Tex tx;
+        float al, c[3], ald = 0.0f, cd[3] = {0.0f, 0.0f, 0.0f};
+        const bool hit = env_value<PD>(G, r, l0 + t, live, X, tx, al, c);
+        if constexpr (TAN) {
+            if (hit) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 w = V(tx.t[q]);
+                    cd[0] += tx.w[q] * w.x;
+                    cd[1] += tx.w[q] * w.y;
+                    cd[2] += tx.w[q] * w.z;
+                    ald += tx.w[q] * w.w;
+                }
+            }
+        }
+        float Tm = T, Tdm = Td;  // in front of the own layer
+        auto pass = [&](float a, float ad, int s) {
+            Tm = t == s ? T : Tm;
+            if constexpr (TAN) {
+                Tdm = t == s ? Td : Tdm;
+                Td = Td * (1.0f - a) - T * ad;
+            }
+            T *= 1.0f - a;
+        };
+        pass(slot_bcast(al, t, 0), slot_bcast(ald, t, 0), 0);
+        pass(slot_bcast(al, t, 1), slot_bcast(ald, t, 1), 1);
+        pass(slot_bcast(al, t, 2), slot_bcast(ald, t, 2), 2);
+        pass(slot_bcast(al, t, 3), slot_bcast(ald, t, 3), 3);
+        const float Ta = Tm * al;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            H[ch] += Ta * c[ch];
+            if constexpr (TAN) Hd[ch] += (Tdm * al + Tm * ald) * c[ch] + Ta * cd[ch];
+        }
+    }
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+        H[ch] = slot_sum(H[ch]) + (live ? T * G.bg[ch] : 0.0f);
+        if constexpr (TAN) Hd[ch] = slot_sum(Hd[ch]) + (live ? Td * G.bg[ch] : 0.0f);
+    }
+}
+
+template <int PD>
+__device__ __forceinline__ void adjoint4(const Geo& G, const Ray& r, bool live, XL<PD> X, const float u[3], float q4,
+                                         Depth depth, Brick4& B, TexTable<4>& TT, float* __restrict__ y) {
+    SinkY sink{y};
+    const int t = slot_id();
+    const float Tx = exp_neg(depth.value());
+    float S[3] = {G.bg[0], G.bg[1], G.bg[2]};
+    {
+        constexpr int kH = kMaxLayers / 4;
+        Tex tx[kH];
+        float al[kH], c[kH][3], Tl[kH];
+        bool hit[kH];
+        float T = Tx;
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            hit[h] = false;
+            al[h] = Tl[h] = c[h][0] = c[h][1] = c[h][2] = 0.0f;
+            if (4 * h < G.n_layers) {
+                hit[h] = env_value<PD>(G, r, 4 * h + t, live, X, tx[h], al[h], c[h]);
+                auto pass = [&](float a, int s) {
+                    Tl[h] = t == s ? T : Tl[h];
+                    T *= 1.0f - a;
+                };
+                pass(slot_bcast(al[h], t, 0), 0);
+                pass(slot_bcast(al[h], t, 1), 1);
+                pass(slot_bcast(al[h], t, 2), 2);
+                pass(slot_bcast(al[h], t, 3), 3);
+            }
+        }
+#pragma unroll
+        for (int h = kH - 1; h >= 0; --h) {
+            if (4 * h < G.n_layers) {
+                float Sb[3] = {0.0f, 0.0f, 0.0f};  // radiance behind the own layer
+                auto pass = [&](float a, float c0, float c1, float c2, int s) {
+#pragma unroll
+                    for (int ch = 0; ch < 3; ++ch) Sb[ch] = t == s ? S[ch] : Sb[ch];
+                    S[0] = a * c0 + (1.0f - a) * S[0];
+                    S[1] = a * c1 + (1.0f - a) * S[1];
+                    S[2] = a * c2 + (1.0f - a) * S[2];
+                };
+                pass(slot_bcast(al[h], t, 3), slot_bcast(c[h][0], t, 3), slot_bcast(c[h][1], t, 3), slot_bcast(c[h][2], t, 3), 3);
+                pass(slot_bcast(al[h], t, 2), slot_bcast(c[h][0], t, 2), slot_bcast(c[h][1], t, 2), slot_bcast(c[h][2], t, 2), 2);
+                pass(slot_bcast(al[h], t, 1), slot_bcast(c[h][0], t, 1), slot_bcast(c[h][1], t, 1), slot_bcast(c[h][2], t, 1), 1);
+                pass(slot_bcast(al[h], t, 0), slot_bcast(c[h][0], t, 0), slot_bcast(c[h][1], t, 0), slot_bcast(c[h][2], t, 0), 0);
+                if (hit[h]) {
+                    const float uc = u[0] * c[h][0] + u[1] * c[h][1] + u[2] * c[h][2];
+                    const float uS = u[0] * Sb[0] + u[1] * Sb[1] + u[2] * Sb[2];
+                    const float A = Tl[h] * al[h];          // dH/dc_l
+                    const float dA = Tl[h] * (uc - uS);     // u . dH/dalpha_l
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float wA = tx[h].w[q] * A;
+                        const float v[4] = {wA * u[0], wA * u[1], wA * u[2], tx[h].w[q] * dA};
+                        TT.insert(tx[h].t[q], v, sink);
+                    }
+                }
+            }
+        }
+    }
+    TT.flush(sink);
+    B.clear_head(16);  // the table's keys (the table's sums are left at zero by the flush)
+    float uG = live ? Tx * (u[0] * S[0] + u[1] * S[1] + u[2] * S[2]) : 0.0f;  // u . G behind the group
+    float Tn = Tx;                                                               // T behind the group
+    const int nx = G.nx, nxy = G.nx * G.ny;
+    const float unit = G.h * G.step;
+    const float t_max = wave_max_f(r.K > 0 ? r.tf : -INFINITY);
+    const int off = r.K > 0 ? (int)((t_max - r.tf) / unit + 0.5f) : 0;
+    const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
+    B.set_direction(r.gd);
+    for (int j = 0; j < J; j += 4) {
+        const int m = j + t - off;
+        const bool on = m >= 0 && m < r.K;
+        const int k = r.K - 1 - m;
+        Corners c{};
+        float dk = 0.0f, tau = 0.0f, uc = 0.0f;
+        if (on) {
+            float g[3], sg, c0, c1, c2;
+            dk = sample_at(G, r, k, g);
+            corners(G, g, c);
+            gather<PD>(X, c, nx, nxy, sg, c0, c1, c2);
+            tau = sg * dk;
+            uc = u[0] * c0 + u[1] * c1 + u[2] * c2;
+        }
+        const float incl = slot_scan(tau);
+        float T = k == 0 ? 1.0f : exp_neg(depth.value() - incl);
+        T = on ? T : Tn;
+        depth.add(-slot_sum(tau));
+        const float Tp = slot_shift<1>(T);
+        const float T1 = t > 0 ? Tp : Tn;  // T_{k+1}
+        Tn = slot_bcast(T, t, 3);
+        const float A = on ? T * one_minus_exp_neg(tau, exp_neg(tau)) : 0.0f;
+        const float behind = slot_scan(A * uc);
+        const float ds = dk * (T1 * uc - (uG + slot_shift<1>(behind)) + q4);
+        uG += slot_sum(A * uc);
+        B.scatter(G, on, c, f4{A * u[0], A * u[1], A * u[2], ds}, sink);
+    }
+    B.flush_all(G, sink);
+}
+
 // ------------------------------------------------------------------ gradient + exact blocks
 // Per-ray window over the current 8 corners.  A voxel is a corner of a contiguous run of
 // a ray's samples (its corner region is a box and the ray is a line), so a voxel that
@@ -1407,20 +1653,30 @@ struct Pix {
     long long ray;
 };
 
-// Workgroup b covers a 16x8 pixel tile of camera b / n_tiles; wave w its 8x8 half w.  With
-// PATCH each row of 16 lanes holds a 4x4 patch of it, else two lines of 8 pixels.
-template <bool PATCH>
+// How a wave's lanes cover its pixels.
+enum Lanes {
+    L_LINES = 0,  // 8x8 pixels, a row of 16 lanes holds two lines of 8
+    L_PATCH = 1,  // 8x8 pixels, a row of 16 lanes holds a 4x4 patch
+    L_SPLIT = 2   // 4x4 pixels, a row of 16 lanes holds a 2x2 quad four times, once per slot
+};
+
+// A workgroup covers a tile of one camera, two waves side by side: 16x8 pixels, 8x4 with L_SPLIT.
+template <int LANES>
 __device__ __forceinline__ Pix pixel_of(const Geo& G) {
+    constexpr int kSide = LANES == L_SPLIT ? 4 : 8;  // pixels along a wave's side
     Pix p;
+    const int tiles_x = LANES == L_SPLIT ? (G.width + 2 * kSide - 1) / (2 * kSide) : G.tiles_x;
+    const int n_tiles = LANES == L_SPLIT ? tiles_x * ((G.height + kSide - 1) / kSide) : G.n_tiles;
     const int b = blockIdx.x;
-    p.cam = b / G.n_tiles;
-    const int tile = b - p.cam * G.n_tiles;
-    const int ty = tile / G.tiles_x, tx = tile - ty * G.tiles_x;
+    p.cam = b / n_tiles;
+    const int tile = b - p.cam * n_tiles;
+    const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int lx = PATCH ? ((lane >> 4) & 1) * 4 + (lane & 3) : lane & 7;
-    const int ly = PATCH ? (lane >> 5) * 4 + ((lane >> 2) & 3) : lane >> 3;
-    p.px = tx * kTileX + wave * 8 + lx;
-    p.py = ty * kTileY + ly;
+    const int qx = (lane >> 4) & 1, qy = lane >> 5;
+    const int lx = LANES == L_SPLIT ? qx * 2 + (lane & 1) : LANES == L_PATCH ? qx * 4 + (lane & 3) : lane & 7;
+    const int ly = LANES == L_SPLIT ? qy * 2 + ((lane >> 1) & 1) : LANES == L_PATCH ? qy * 4 + ((lane >> 2) & 3) : lane >> 3;
+    p.px = tx * 2 * kSide + wave * kSide + lx;
+    p.py = ty * kSide + ly;
     p.active = p.px < G.width && p.py < G.height;
     p.ray = ((long long)p.cam * G.height + p.py) * G.width + p.px;
     return p;
@@ -1433,7 +1689,7 @@ struct Lds {
     static constexpr int WAVES = (MODE == M_VJP || MODE == M_JTJ) ? 4 : 1;  // waves per SIMD to leave registers for
 };
 
-template <int MODE, int PD>
+template <int MODE, int PD, bool SPLIT>
 __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs A) {
     constexpr int NCH = Lds<MODE>::NCH;
     constexpr bool SCATTER = Lds<MODE>::SCATTER;
@@ -1442,7 +1698,8 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
     __shared__ f4 s_brick4[JT ? kWaves * kB3 : 1];
     __shared__ f4 s_stage[JT ? kWaves * kStageRow : 1];
     if (A.done && *A.done) return;
-    const Pix p = pixel_of<JT>(G);
+    const Pix p = pixel_of<SPLIT ? L_SPLIT : MODE == M_GRAD ? L_LINES : L_PATCH>(G);
+    const bool first = !SPLIT || (threadIdx.x & 12) == 0;  // the lane that writes the ray's results
     const int wave = threadIdx.x >> 6;
     const int units = G.nvox + G.n_layers * G.env_w * G.env_h;
     XL<PD> X;
@@ -1458,10 +1715,12 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
     if constexpr (MODE == M_JVP || MODE == M_JTJ) {
         VecF4 V;
         V.r = make_rsrc(A.v, (unsigned)units * VecF4::kBytes);
-        forward<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth);
+        if constexpr (SPLIT) forward4<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f);
+        else forward<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth);
     } else {
-        forward<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth,
-                           MODE == M_RENDER ? A.thresh : 0.0f);
+        const float thresh = MODE == M_RENDER ? A.thresh : 0.0f;
+        if constexpr (SPLIT) forward4<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
+        else forward<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
     }
     // auxiliary opacity residual (Sec. III-I, Eq. 10): r4 = lambda (1 - 4 (T - 1/2)^2) =
     // 4 lambda T (1 - T) with T the transmittance through the volume; dr4/dT = 4 lambda (1 - 2T)
@@ -1471,7 +1730,7 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
     const int nres = A.nres;
     double rr_sum = 0.0;
     if constexpr (MODE == M_RENDER) {
-        if (p.active) {
+        if (p.active && first) {
             if (A.targets) {
                 float res[3];
 #pragma unroll
@@ -1491,7 +1750,7 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
             }
         }
     } else if constexpr (MODE == M_JVP) {
-        if (p.active) {
+        if (p.active && first) {
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) A.rout[nres * p.ray + ch] = Hd[ch];
             if (aux) A.rout[nres * p.ray + 3] = dr4 * Tdexit;  // d r4 = dr4/dT * dT
@@ -1522,7 +1781,8 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
             // u4 d r4 / d sigma_k = u4 dr4/dT (-T delta_k): a per-ray constant times delta_k,
             // added to the sigma partial of every sample
             const float q4 = -u4 * dr4 * Texit;
-            adjoint_scatter<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
+            if constexpr (SPLIT) adjoint4<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
+            else adjoint_scatter<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
         } else {
             BrickAtomic<NCH> B;
             B.init((float*)(s_brick + wave * NCH * kB3 / 4));
@@ -1552,7 +1812,7 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
 // already corners of the previous sample (per-axis sets of one or two indices).
 __global__ __launch_bounds__(kBlock) void k_footprint(Geo G, const DevCam* cams, int32_t* per_ray,
                                                       unsigned long long* totals) {
-    const Pix p = pixel_of<false>(G);
+    const Pix p = pixel_of<L_LINES>(G);
     unsigned long long U = 0, nl = 0, hit = 0;
     if (p.active) {
         Ray r;
@@ -1602,31 +1862,40 @@ __global__ __launch_bounds__(kBlock) void k_footprint(Geo G, const DevCam* cams,
     }
 }
 
-template <int MODE, int PD>
+template <int MODE, int PD, bool SPLIT>
 hipError_t launch_one(const Geo& g, const RayArgs& a, hipStream_t st) {
-    const unsigned grid = (unsigned)((long long)g.n_cams * g.n_tiles);
+    const unsigned grid = (unsigned)ray_blocks(g, SPLIT);
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_ray<MODE, PD>), dim3(grid), dim3(kBlock), 0, st, g, a);
+    hipLaunchKernelGGL((k_ray<MODE, PD, SPLIT>), dim3(grid), dim3(kBlock), 0, st, g, a);
     return hipGetLastError();
 }
 
-template <int PD>
+template <int PD, bool SPLIT>
 hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st) {
     switch (mode) {
-        case M_RENDER: return launch_one<M_RENDER, PD>(g, a, st);
-        case M_JVP: return launch_one<M_JVP, PD>(g, a, st);
-        case M_VJP: return launch_one<M_VJP, PD>(g, a, st);
-        case M_JTJ: return launch_one<M_JTJ, PD>(g, a, st);
-        case M_GRAD: return launch_one<M_GRAD, PD>(g, a, st);
+        case M_RENDER: return launch_one<M_RENDER, PD, SPLIT>(g, a, st);
+        case M_JVP: return launch_one<M_JVP, PD, SPLIT>(g, a, st);
+        case M_VJP: return launch_one<M_VJP, PD, SPLIT>(g, a, st);
+        case M_JTJ: return launch_one<M_JTJ, PD, SPLIT>(g, a, st);
+        case M_GRAD: return launch_one<M_GRAD, PD, false>(g, a, st);
         default: return hipErrorInvalidValue;
     }
 }
 
 }  // namespace
 
+int64_t ray_blocks(const Geo& g, bool split) {
+    const int64_t w = split ? kTileX / 2 : kTileX, h = split ? kTileY / 2 : kTileY;
+    return (int64_t)g.n_cams * ((g.width + w - 1) / w) * ((g.height + h - 1) / h);
+}
+
+bool split_rays(int mode, const Geo& g) { return mode != M_GRAD && ray_blocks(g, false) < 2048; }
+
 hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st) {
-    if (param_dtype == PERF_BF16) return launch_mode<PERF_BF16>(mode, g, a, st);
-    return launch_mode<PERF_F32>(mode, g, a, st);
+    const bool split = split_rays(mode, g);
+    if (param_dtype == PERF_BF16)
+        return split ? launch_mode<PERF_BF16, true>(mode, g, a, st) : launch_mode<PERF_BF16, false>(mode, g, a, st);
+    return split ? launch_mode<PERF_F32, true>(mode, g, a, st) : launch_mode<PERF_F32, false>(mode, g, a, st);
 }
 
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,
