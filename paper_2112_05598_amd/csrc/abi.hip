@@ -92,6 +92,20 @@ int32_t validate(const perf_scene_desc* d, int n_cams) {
     return PERF_OK;
 }
 
+// Mean over the cameras of a pixel's width at the distance of the grid's centre, in units of h.
+float mean_pitch(const perf_scene_desc& d, const perf_camera* cams, int n_cams, float h) {
+    double sum = 0.0;
+    for (int c = 0; c < n_cams; ++c) {
+        double r2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double v = 0.5 * ((double)d.bbox_min[a] + d.bbox_max[a]) - cams[c].origin[a];
+            r2 += v * v;
+        }
+        sum += sqrt(r2 / fabs((double)cams[c].fx * cams[c].fy));
+    }
+    return (float)(sum / n_cams / h);
+}
+
 }  // namespace
 
 namespace perf {
@@ -132,7 +146,7 @@ Layout make_layout(const perf_scene_desc& d, int n_cams) {
     const int64_t units = (int64_t)d.nx * d.ny * d.nz + (int64_t)d.n_layers * d.env_w * d.env_h;
     const int64_t P = 4 * units;
     const Geo g = make_geo(d, n_cams);
-    L.n_partials = std::max<int64_t>(2 * kVecGrid, std::max(ray_blocks(g, false), split_rays(M_RENDER, g) ? ray_blocks(g, true) : 0));
+    L.n_partials = std::max<int64_t>(2 * kVecGrid, std::max(ray_blocks(g, false), ray_blocks(g, true)));
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -205,6 +219,7 @@ int32_t perf_init_scene(const perf_scene_desc* desc, const perf_camera* cams, in
     s->desc = *desc;
     s->n_cams = n_cams;
     s->geo = make_geo(*desc, n_cams);
+    s->geo.pitch = mean_pitch(*desc, cams, n_cams, s->geo.h);
     s->lay = L;
     s->ws = (char*)d_workspace;
     s->targets = d_targets;

@@ -35,6 +35,7 @@ struct Geo {
     float radius[kMaxLayers];
     float bg[3];
     int nvox;         // voxel units; texel units follow
+    float pitch;      // mean width of a pixel at the grid's centre, in units of h (split_rays)
     unsigned jseed;   // jittering seed (Sec. IV), 0 = pixel centres and step midpoints
 };
 

@@ -284,15 +284,6 @@ __device__ __forceinline__ float one_minus_exp_neg(float t, float e) {
     return fabsf(t) < 0.25f ? series : 1.0f - e;
 }
 
-// ------------------------------------------------------------------ lane swaps (DPP)
-// Value of lane ^ 1 (quad permutation 1,0,3,2), of lane ^ 2 (quad permutation 2,3,0,1) and of
-// lane ^ 8 (rotation by 8 inside each row of 16 lanes).  Called with every lane of the wave active.
-__device__ __forceinline__ int dpp_xor1(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true); }
-__device__ __forceinline__ int dpp_xor2(int v) { return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true); }
-__device__ __forceinline__ int dpp_row_xor8(int v) { return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true); }
-__device__ __forceinline__ float dpp_xor1(float v) { return __int_as_float(dpp_xor1(__float_as_int(v))); }
-__device__ __forceinline__ float dpp_row_xor8(float v) { return __int_as_float(dpp_row_xor8(__float_as_int(v))); }
-
 // ------------------------------------------------------------------ wave helpers
 // minimum / maximum over the wave: inside each row of 16 lanes by DPP rotations, then over the
 // four rows in scalar registers
@@ -330,8 +321,8 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ void lds_add(__attribute__((address_space(3))) float* p, float v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
-__device__ __forceinline__ float lds_take(__attribute__((address_space(3))) float* p) {
-    return __hip_atomic_exchange(p, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+__device__ __forceinline__ void lds_add(__attribute__((address_space(3))) double* p, double v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 // ------------------------------------------------------------------ per-wave scatter combining
@@ -367,78 +358,19 @@ constexpr int kStageRow = 68;  // 16 float4 of a row and 4 floats of padding: th
 #define LDS __attribute__((address_space(3)))
 typedef LDS f4 lds_f4;
 typedef LDS float lds_float;
+typedef LDS double lds_double;
 typedef LDS int lds_int;
 
 __device__ __forceinline__ int ring_slot(int x, int y, int z) {
     return ((z & (kB - 1)) * kB + (y & (kB - 1))) * kB + (x & (kB - 1));
 }
 
-// Window bookkeeping shared by the accumulator kinds: origin, fit and slab iteration.
+// The window's origin (voxel coordinates, wave-uniform).
 struct Window {
-    int o[3];  // window origin (voxel coordinates), wave-uniform
+    int o[3];
     __device__ __forceinline__ bool inside(const int lo[3], const int hi[3]) const {
         return lo[0] >= o[0] && hi[0] < o[0] + kB && lo[1] >= o[1] && hi[1] < o[1] + kB && lo[2] >= o[2] &&
                hi[2] < o[2] + kB;
-    }
-    // coordinate of the window along axis a that sits in ring slot sa
-    __device__ __forceinline__ int coord(int a, int sa) const { return o[a] + ((sa - o[a]) & (kB - 1)); }
-    // flush(x, y, z) for every window voxel, one per lane per round
-    template <class Flush>
-    __device__ __forceinline__ void each_voxel(Flush& flush) const {
-        for (int i = lane_id(); i < kB3; i += 64) {
-            const int sx = i & (kB - 1), sy = (i >> 3) & (kB - 1), sz = i >> 6;
-            flush(coord(0, sx), coord(1, sy), coord(2, sz));
-        }
-    }
-    template <class Flush>
-    __device__ __forceinline__ void move_axis(int a, int no, Flush& flush) {
-        const int d = no - o[a];
-        if (d == 0) return;
-        if (d >= kB || d <= -kB) {
-            each_voxel(flush);
-        } else {
-            const int first = d > 0 ? o[a] : o[a] + kB + d;
-            const int cnt = d > 0 ? d : -d;
-            const int p = lane_id() & (kB - 1), q = lane_id() >> 3;
-            const int b1 = a == 0 ? 1 : 0, b2 = a == 2 ? 1 : 2;
-            const int v1 = coord(b1, p), v2 = coord(b2, q);
-            for (int t = 0; t < cnt; ++t) {
-                int c[3];
-                c[a] = first + t;
-                c[b1] = v1;
-                c[b2] = v2;
-                flush(c[0], c[1], c[2]);
-            }
-        }
-        o[a] = no;
-    }
-    // New origin `no` that covers the corner boxes [lo, hi] of every lane that is on; false if the
-    // window covers them already.
-    __device__ __forceinline__ bool target(bool on, const int lo[3], const int hi[3], int no[3]) const {
-        const bool fits = !on || inside(lo, hi);
-        if (!wave_any(!fits)) return false;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int mn = wave_min_i(on ? lo[a] : (1 << 30));
-            const int mx = wave_max_i(on ? hi[a] : -(1 << 30));
-            no[a] = o[a];
-            if (mn > mx) continue;  // no lane on
-            if (mx - mn < kB) {
-                if (mn < no[a]) no[a] = mn;
-                else if (mx > no[a] + kB - 1) no[a] = mx - kB + 1;
-            } else if (mn < no[a] || mn > no[a] + kB - 1) {
-                no[a] = mn;  // cannot cover every lane: keep the low end, the rest go to HBM
-            }
-        }
-        return true;
-    }
-    // Make the window cover the corner boxes [lo, hi] of every lane that is on.
-    template <class Flush>
-    __device__ __forceinline__ void fit(bool on, const int lo[3], const int hi[3], Flush& flush) {
-        int no[3];
-        if (!target(on, lo, hi, no)) return;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) move_axis(a, no[a], flush);
     }
 };
 
@@ -526,9 +458,6 @@ struct Brick4 {
             c += d > 0 ? 1 : -1;
         }
         win.o[A] = no;
-    }
-    __device__ __forceinline__ void clear_head(int n) {
-        for (int i = lane_id(); i < n; i += 64) s[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     }
     // Add box Q to the window and clear it; voxels the window does not cover go to HBM.
     template <int Q, class Sink>
@@ -705,53 +634,6 @@ struct Brick4 {
     }
 };
 
-// Accumulator with NCH scalar channels updated by LDS atomics: the gradient pass flushes
-// per-ray window sums that many lanes of a wave hand over for one voxel at the same step,
-// where atomics serialise more cheaply than elections.
-template <int NCH>
-struct BrickAtomic {
-    Window win;
-    lds_float* s;  // [NCH][kB3]
-
-    __device__ __forceinline__ void init(float* base) {
-        s = (lds_float*)base;
-        win.o[0] = win.o[1] = win.o[2] = -(1 << 24);
-        for (int i = lane_id(); i < NCH * kB3; i += 64) s[i] = 0.0f;
-    }
-    __device__ __forceinline__ bool inside(const int lo[3], const int hi[3]) const { return win.inside(lo, hi); }
-    // zero the first n floats (the texel table's keys after its flush)
-    __device__ __forceinline__ void clear_head(int n) {
-        for (int i = lane_id(); i < n; i += 64) s[i] = 0.0f;
-    }
-    __device__ __forceinline__ void add(int x, int y, int z, const float v[NCH]) {
-        const int sl = ring_slot(x, y, z);
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) lds_add(s + c * kB3 + sl, v[c]);
-    }
-    template <class F>
-    __device__ __forceinline__ void flush_voxel(const Geo& G, int x, int y, int z, F& out) {
-        const int sl = ring_slot(x, y, z);
-        float v[NCH];
-        bool nz = false;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            v[c] = lds_take(s + c * kB3 + sl);
-            nz |= v[c] != 0.0f;
-        }
-        if (nz && x >= 0 && y >= 0 && z >= 0 && x < G.nx && y < G.ny && z < G.nz) out((z * G.ny + y) * G.nx + x, v);
-    }
-    template <class F>
-    __device__ __forceinline__ void flush_all(const Geo& G, F& out) {
-        auto fl = [&](int x, int y, int z) { flush_voxel(G, x, y, z, out); };
-        win.each_voxel(fl);
-    }
-    template <class F>
-    __device__ __forceinline__ void fit(const Geo& G, bool on, const int lo[3], const int hi[3], F& out) {
-        auto fl = [&](int x, int y, int z) { flush_voxel(G, x, y, z, out); };
-        win.fit(on, lo, hi, fl);
-    }
-};
-
 __device__ __forceinline__ int __hip_atomic_compare_exchange_strong_ret(lds_int* p, int expected, int desired) {
     __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -762,14 +644,15 @@ __device__ __forceinline__ int __hip_atomic_compare_exchange_strong_ret(lds_int*
 // probing; a texel that finds no slot goes straight to a global atomic).
 template <int NCH>
 struct TexTable {
+    static constexpr int kDoubles = 32 + NCH * 64;  // LDS it takes: the keys, then the sums (in double, BrickAtomic)
     lds_int* keys;  // [64]
-    lds_float* s;   // [NCH][64]
-    __device__ __forceinline__ void init(int* kbase, float* sbase) {
-        keys = (lds_int*)kbase;
-        s = (lds_float*)sbase;
+    lds_double* s;  // [NCH][64]
+    __device__ __forceinline__ void init(double* base) {
+        keys = (lds_int*)base;
+        s = (lds_double*)(base + 32);
         keys[lane_id()] = -1;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) s[c * 64 + lane_id()] = 0.0f;
+        for (int c = 0; c < NCH; ++c) s[c * 64 + lane_id()] = 0.0;
     }
     template <class F>
     __device__ __forceinline__ void insert(int t, const float v[NCH], F& out) {
@@ -779,20 +662,27 @@ struct TexTable {
             const int prev = __hip_atomic_compare_exchange_strong_ret(keys + sl, -1, t);
             if (prev == -1 || prev == t) {
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) lds_add(s + c * 64 + sl, v[c]);
+                for (int c = 0; c < NCH; ++c) lds_add(s + c * 64 + sl, (double)v[c]);
                 return;
             }
             sl = (sl + 1) & 63;
         }
         out(t, v);
     }
+    // hand the sums to HBM; the table's LDS is left zeroed
     template <class F>
     __device__ __forceinline__ void flush(F& out) {
         const int l = lane_id();
-        const int t = __hip_atomic_exchange(keys + l, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        wave_fence();
+        const int t = keys[l];
+        keys[l] = 0;
         float v[NCH];
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) v[c] = lds_take(s + c * 64 + l);
+        for (int c = 0; c < NCH; ++c) {
+            v[c] = (float)s[c * 64 + l];
+            s[c * 64 + l] = 0.0;
+        }
+        wave_fence();
         if (t >= 0) out(t, v);
     }
 };
@@ -828,7 +718,126 @@ struct SinkGrad {  // grad[4u + c] (c < 4) and blocks[5u + c] (channels 4..8)
                 if (v[4 + c] != 0.0f) atomic_add(b + c, v[4 + c]);
         }
     }
+    // one channel of the gradient (32-bit byte offset) or of the block
+    __device__ __forceinline__ void one(bool of_grad, int u, int c, float v) const {
+        if (of_grad) {
+            if (grad) atomic_add((float*)((char*)grad + (16u * (unsigned)u + 4u * (unsigned)c)), v);
+        } else if (blocks) {
+            atomic_add(blocks + 5 * (size_t)u + c, v);
+        }
+    }
 };
+
+// The gradient pass's accumulator: nine channels (gradient, block) per voxel of a 6x6x6 window,
+// updated by LDS atomics (neighbouring rays hand over the same voxel at the same step).  The
+// sums are in double because the double add is the fast one: an LDS float atomic takes about
+// 3 cycles per active lane whatever the addresses (196 cycles for a full wave), the double one 10
+// cycles for a wave of distinct addresses and 3 for each lane that shares one.  Only the voxels that
+// leave the rays' register windows have to fit, and 6 voxels along each axis cover 99.6 % of them
+// for an 8x8 tile with pixels 0.47 voxels apart; 15.5 KB a wave leave room for 10 waves per CU (8x8x8
+// voxels took 37 KB, 4 waves).  The rest goes straight to HBM.
+struct GradBrick {
+    static constexpr int kW = 6, kW3 = kW * kW * kW, kCh = 9;
+    // Place of ring slot r of an axis: the voxels of one parity class (they are added together) are 27
+    // consecutive doubles, so distinct ones never share a bank.
+    template <int A>
+    static __device__ __forceinline__ int place(int r) {
+        constexpr int kHalf[3] = {1, 9, 3}, kOdd[3] = {27, 54, 108};
+        return (r >> 1) * kHalf[A] + (r & 1) * kOdd[A];
+    }
+    int o[3];    // low corner (wave-uniform)
+    int rs[3];   // ring slot of the low corner along each axis (wave-uniform)
+    bool up[3];  // the march goes towards +axis (wave-uniform)
+    lds_double* s;  // [kCh][kW3]
+
+    __device__ __forceinline__ void init(double* base, const float gd[3]) {
+        s = (lds_double*)base;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            up[a] = __builtin_amdgcn_readfirstlane(__float_as_int(gd[a])) < 0;
+            o[a] = up[a] ? -(1 << 24) : (1 << 29);
+            rs[a] = 0;
+        }
+        for (int i = lane_id(); i < kCh * kW3; i += 64) s[i] = 0.0;
+    }
+    __device__ __forceinline__ int wrap(int r) const { return (int)min((unsigned)r, (unsigned)(r - kW)); }
+    // place of a coordinate inside the window
+    template <int A>
+    __device__ __forceinline__ int at(int c) const { return place<A>(wrap(c - o[A] + rs[A])); }
+    __device__ __forceinline__ bool inside(int a, int c) const { return (unsigned)(c - o[a]) < (unsigned)kW; }
+    __device__ __forceinline__ void add(int sl, const float v[kCh]) {
+#pragma unroll
+        for (int c = 0; c < kCh; ++c) lds_add(s + c * kW3 + sl, (double)v[c]);
+    }
+    // Flush the plane at coordinate c of axis A (ring slot rc): the gradient with four lanes per voxel,
+    // the blocks with five, so that neighbouring lanes add to neighbouring addresses.
+    template <int A>
+    __device__ __forceinline__ void flush_plane(const Geo& G, int c, int rc, const SinkGrad& out) {
+        const int n[3] = {G.nx, G.ny, G.nz};
+        if (c < 0 || c >= n[A]) return;  // outside the grid nothing is added
+        constexpr int P = A == 0 ? 1 : 0, Q = A == 2 ? 1 : 2;
+        const int pitch[3] = {1, G.nx, G.nx * G.ny};
+        const int pc = place<A>(rc);
+        wave_fence();
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            const bool gr = r < 3;  // rounds 0 .. 2: gradient, 3 .. 5: blocks
+            const int e = lane_id() + 64 * (gr ? r : r - 3);
+            const int v = gr ? e >> 2 : (e * 13108) >> 16;  // e / 5
+            const int ch = gr ? e & 3 : e - 5 * v;
+            const int q = (v * 10923) >> 16, p = v - kW * q;  // v / 6
+            const int cp = o[P] + p, cq = o[Q] + q;
+            if (v < kW * kW) {
+                lds_double* d = s + (gr ? ch : 4 + ch) * kW3 + pc + place<P>(wrap(p + rs[P])) + place<Q>(wrap(q + rs[Q]));
+                const float f = (float)*d;
+                *d = 0.0;
+                if (f != 0.0f && (unsigned)cp < (unsigned)n[P] && (unsigned)cq < (unsigned)n[Q])
+                    out.one(gr, c * pitch[A] + cp * pitch[P] + cq * pitch[Q], ch, f);
+            }
+        }
+        wave_fence();
+    }
+    template <int A>
+    __device__ __forceinline__ void move_axis(const Geo& G, int no, const SinkGrad& out) {
+        const int d = up[A] ? no - o[A] : o[A] - no;  // never negative
+        if (d == 0) return;
+        const int cnt = min(d, kW);
+        int c = up[A] ? o[A] : o[A] + kW - 1, rc = up[A] ? rs[A] : wrap(rs[A] + kW - 1);
+#pragma unroll 1
+        for (int t = 0; t < cnt; ++t) {
+            flush_plane<A>(G, c, rc, out);
+            c += up[A] ? 1 : -1;
+            rc = up[A] ? (rc == kW - 1 ? 0 : rc + 1) : (rc == 0 ? kW - 1 : rc - 1);
+        }
+        // going up the freed slots follow the last one, going down they lead
+        rs[A] = up[A] ? rc : (rc == kW - 1 ? 0 : rc + 1);
+        o[A] = no;
+    }
+    // Move the window so that the boxes [lo, hi] of every lane that is on lie inside on the side the
+    // march goes to.
+    __device__ __forceinline__ void fit(const Geo& G, bool on, const int lo[3], const int hi[3], const SinkGrad& out) {
+        bool in = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) in &= up[a] ? hi[a] < o[a] + kW : lo[a] >= o[a];
+        if (!wave_any(on && !in)) return;
+        int no[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            no[a] = up[a] ? max(o[a], wave_max_i(on ? hi[a] : -(1 << 30)) - kW + 1) : min(o[a], wave_min_i(on ? lo[a] : (1 << 30)));
+        move_axis<0>(G, no[0], out);
+        move_axis<1>(G, no[1], out);
+        move_axis<2>(G, no[2], out);
+    }
+    __device__ __forceinline__ void flush_all(const Geo& G, const SinkGrad& out) {
+        int rc = rs[2];
+#pragma unroll 1
+        for (int t = 0; t < kW; ++t) {
+            flush_plane<2>(G, o[2] + t, rc, out);
+            rc = rc == kW - 1 ? 0 : rc + 1;
+        }
+    }
+};
+
 // ------------------------------------------------------------------ forward pass (+ tangent)
 // Optical depth in front of a sample, summed with compensation (Kahan) so that the
 // adjoint pass can step it back sample by sample with an error of order eps * V_total.
@@ -1103,6 +1112,21 @@ __device__ __forceinline__ void env_back(const Geo& G, const Ray& r, XL<PD> X, f
 // Voxel samples from the last to the first, as in Alg. 1: G_k (colour composited behind
 // sample k) is accumulated from the back starting at the environment seen from the exit,
 // and T_k = exp(-V_k) with V_k the compensated optical depth stepped back.
+// One layer's contribution u . dH/d(texels).
+__device__ __forceinline__ void jt_layer(const Tex& tx, const float c[3], float al, float Tl, const float Sb[3],
+                                         const float u[3], TexTable<4>& TT, SinkY& sink) {
+    const float uc = u[0] * c[0] + u[1] * c[1] + u[2] * c[2];
+    const float uS = u[0] * Sb[0] + u[1] * Sb[1] + u[2] * Sb[2];
+    const float A = Tl * al;          // dH/dc_l
+    const float dA = Tl * (uc - uS);  // u . dH/dalpha_l
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float wA = tx.w[j] * A;
+        const float v[4] = {wA * u[0], wA * u[1], wA * u[2], tx.w[j] * dA};
+        TT.insert(tx.t[j], v, sink);
+    }
+}
+
 template <int PD>
 __device__ __forceinline__ void adjoint_scatter(const Geo& G, const Ray& r, bool live, XL<PD> X, const float u[3],
                                                 float q4, Depth depth, Brick4& B, TexTable<4>& TT,
@@ -1113,22 +1137,12 @@ __device__ __forceinline__ void adjoint_scatter(const Geo& G, const Ray& r, bool
     if (live) {
         float S[3];
         auto emit = [&](const Tex& tx, const float c[3], float al, float Tl, const float Sb[3]) {
-            const float uc = u[0] * c[0] + u[1] * c[1] + u[2] * c[2];
-            const float uS = u[0] * Sb[0] + u[1] * Sb[1] + u[2] * Sb[2];
-            const float A = Tl * al;          // dH/dc_l
-            const float dA = Tl * (uc - uS);  // u . dH/dalpha_l
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float wA = tx.w[j] * A;
-                const float v[4] = {wA * u[0], wA * u[1], wA * u[2], tx.w[j] * dA};
-                TT.insert(tx.t[j], v, sink);
-            }
+            jt_layer(tx, c, al, Tl, Sb, u, TT, sink);
         };
         env_back<PD>(G, r, X, Tx, S, emit);
         uE = u[0] * S[0] + u[1] * S[1] + u[2] * S[2];
     }
     TT.flush(sink);
-    B.clear_head(16);  // the table's keys (the table's sums are left at zero by the flush)
     float uG = Tx * uE;  // u . G_k
     float Tn = Tx;       // T_{k+1}
     const int nx = G.nx, nxy = G.nx * G.ny;
@@ -1313,67 +1327,62 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
     }
 }
 
+// env_back with one layer per slot; S starts at the background and ends as the radiance seen from
+// the grid exit in every slot.
+template <int PD, class Emit>
+__device__ __forceinline__ void env_back4(const Geo& G, const Ray& r, bool live, XL<PD> X, float Tx, float S[3],
+                                          Emit& emit) {
+    const int t = slot_id();
+    constexpr int kH = kMaxLayers / 4;
+    Tex tx[kH];
+    float al[kH], c[kH][3], Tl[kH];
+    bool hit[kH];
+    float T = Tx;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) S[ch] = G.bg[ch];
+#pragma unroll
+    for (int h = 0; h < kH; ++h) {
+        hit[h] = false;
+        al[h] = Tl[h] = c[h][0] = c[h][1] = c[h][2] = 0.0f;
+        if (4 * h < G.n_layers) {
+            hit[h] = env_value<PD>(G, r, 4 * h + t, live, X, tx[h], al[h], c[h]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                Tl[h] = t == s ? T : Tl[h];
+                T *= 1.0f - slot_bcast(al[h], t, s);
+            }
+        }
+    }
+#pragma unroll
+    for (int h = kH - 1; h >= 0; --h) {
+        if (4 * h < G.n_layers) {
+            float Sb[3] = {0.0f, 0.0f, 0.0f};  // radiance behind the own layer
+#pragma unroll
+            for (int s = 3; s >= 0; --s) {
+                const float a = slot_bcast(al[h], t, s);
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) {
+                    Sb[ch] = t == s ? S[ch] : Sb[ch];
+                    S[ch] = a * slot_bcast(c[h][ch], t, s) + (1.0f - a) * S[ch];
+                }
+            }
+            if (hit[h]) emit(tx[h], c[h], al[h], Tl[h], Sb);
+        }
+    }
+}
+
 template <int PD>
 __device__ __forceinline__ void adjoint4(const Geo& G, const Ray& r, bool live, XL<PD> X, const float u[3], float q4,
                                          Depth depth, Brick4& B, TexTable<4>& TT, float* __restrict__ y) {
     SinkY sink{y};
     const int t = slot_id();
     const float Tx = exp_neg(depth.value());
-    float S[3] = {G.bg[0], G.bg[1], G.bg[2]};
-    {
-        constexpr int kH = kMaxLayers / 4;
-        Tex tx[kH];
-        float al[kH], c[kH][3], Tl[kH];
-        bool hit[kH];
-        float T = Tx;
-#pragma unroll
-        for (int h = 0; h < kH; ++h) {
-            hit[h] = false;
-            al[h] = Tl[h] = c[h][0] = c[h][1] = c[h][2] = 0.0f;
-            if (4 * h < G.n_layers) {
-                hit[h] = env_value<PD>(G, r, 4 * h + t, live, X, tx[h], al[h], c[h]);
-                auto pass = [&](float a, int s) {
-                    Tl[h] = t == s ? T : Tl[h];
-                    T *= 1.0f - a;
-                };
-                pass(slot_bcast(al[h], t, 0), 0);
-                pass(slot_bcast(al[h], t, 1), 1);
-                pass(slot_bcast(al[h], t, 2), 2);
-                pass(slot_bcast(al[h], t, 3), 3);
-            }
-        }
-#pragma unroll
-        for (int h = kH - 1; h >= 0; --h) {
-            if (4 * h < G.n_layers) {
-                float Sb[3] = {0.0f, 0.0f, 0.0f};  // radiance behind the own layer
-                auto pass = [&](float a, float c0, float c1, float c2, int s) {
-#pragma unroll
-                    for (int ch = 0; ch < 3; ++ch) Sb[ch] = t == s ? S[ch] : Sb[ch];
-                    S[0] = a * c0 + (1.0f - a) * S[0];
-                    S[1] = a * c1 + (1.0f - a) * S[1];
-                    S[2] = a * c2 + (1.0f - a) * S[2];
-                };
-                pass(slot_bcast(al[h], t, 3), slot_bcast(c[h][0], t, 3), slot_bcast(c[h][1], t, 3), slot_bcast(c[h][2], t, 3), 3);
-                pass(slot_bcast(al[h], t, 2), slot_bcast(c[h][0], t, 2), slot_bcast(c[h][1], t, 2), slot_bcast(c[h][2], t, 2), 2);
-                pass(slot_bcast(al[h], t, 1), slot_bcast(c[h][0], t, 1), slot_bcast(c[h][1], t, 1), slot_bcast(c[h][2], t, 1), 1);
-                pass(slot_bcast(al[h], t, 0), slot_bcast(c[h][0], t, 0), slot_bcast(c[h][1], t, 0), slot_bcast(c[h][2], t, 0), 0);
-                if (hit[h]) {
-                    const float uc = u[0] * c[h][0] + u[1] * c[h][1] + u[2] * c[h][2];
-                    const float uS = u[0] * Sb[0] + u[1] * Sb[1] + u[2] * Sb[2];
-                    const float A = Tl[h] * al[h];          // dH/dc_l
-                    const float dA = Tl[h] * (uc - uS);     // u . dH/dalpha_l
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float wA = tx[h].w[q] * A;
-                        const float v[4] = {wA * u[0], wA * u[1], wA * u[2], tx[h].w[q] * dA};
-                        TT.insert(tx[h].t[q], v, sink);
-                    }
-                }
-            }
-        }
-    }
+    float S[3];
+    auto emit = [&](const Tex& tx, const float c[3], float al, float Tl, const float Sb[3]) {
+        jt_layer(tx, c, al, Tl, Sb, u, TT, sink);
+    };
+    env_back4<PD>(G, r, live, X, Tx, S, emit);
     TT.flush(sink);
-    B.clear_head(16);  // the table's keys (the table's sums are left at zero by the flush)
     float uG = live ? Tx * (u[0] * S[0] + u[1] * S[1] + u[2] * S[2]) : 0.0f;  // u . G behind the group
     float Tn = Tx;                                                               // T behind the group
     const int nx = G.nx, nxy = G.nx * G.ny;
@@ -1420,126 +1429,69 @@ __device__ __forceinline__ void adjoint4(const Geo& G, const Ray& r, bool live, 
 // voxel whose coordinate parities are the bits of b, so a voxel entering the window takes
 // the slot of the one that left and nothing moves.  The flushed per-ray products
 // (gradient and block entries, linear in the rays) are combined per wave in LDS.
+//
+// With SPLIT a wave covers 4x4 pixels and the four lanes of a ray (slots, forward4) own two of its
+// window's voxels each, those with x and y parities t & 1 and t >> 1: each lane loads, weighs and
+// flushes its own two, and the interpolated sample is the sum over the four.
+template <int NS>
 struct GradWin {
-    int i[3];                                 // low corner of the window
-    float a[8], s0[8], s1[8], s2[8], s3[8];   // per slot: sum w A, sum w d_sigma (3 colours), sum w delta
+    float a[NS], s0[NS], s1[NS], s2[NS], s3[NS];  // sum w A, sum w d_sigma (3 colours), sum w delta
 };
 
-// slots whose voxel leaves when the window's low corner moves from w to c (at most one cell
-// per axis per sample; a larger jump empties the whole window)
-__device__ __forceinline__ unsigned leaving_slots(const int w[3], const int c[3]) {
-    constexpr unsigned kBit0[3] = {0x55u, 0x33u, 0x0Fu};  // slots with bit a = 0
-    unsigned m = 0u;
+// Adds the products of a lane and its partner (DPP swap CTRL) where both are in `left` with one voxel
+// `at`; of the two the lane in `keep` stays.  Called with every lane active.
+template <int CTRL>
+__device__ __forceinline__ void grad_fold(int at, float v[9], unsigned long long& left, unsigned long long keep) {
+    const int key = __builtin_amdgcn_inverse_ballot_w64(left) ? at : -1;
+    const int other = __builtin_amdgcn_mov_dpp(key, CTRL, 0xF, 0xF, true);
+    const unsigned long long both = __ballot(other == at) & left;
+    if (__builtin_amdgcn_inverse_ballot_w64(both)) {  // holds for both lanes of a pair
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int d = c[a] - w[a];
-        if (d != 0) {
-            const int gone = d > 0 ? w[a] : w[a] + 1;  // coordinate left behind
-            m |= (d > 1 || d < -1) ? 0xFFu : ((gone & 1) ? (~kBit0[a] & 0xFFu) : kBit0[a]);
-        }
+        for (int c = 0; c < 9; ++c)
+            v[c] += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v[c]), CTRL, 0xF, 0xF, true));
     }
-    return m;
+    left &= ~both | keep;
 }
 
-template <int SLOT>
-__device__ __forceinline__ void grad_flush_slot(const Geo& G, unsigned pend, const GradWin& w, const float rr[3],
-                                                float r4, float g4, BrickAtomic<9>& B, const SinkGrad& sink) {
-    const bool mine = (pend >> SLOT) & 1u;
-    if (!wave_any(mine)) return;
-    const int x = w.i[0] + (((SLOT >> 0) ^ w.i[0]) & 1);
-    const int y = w.i[1] + (((SLOT >> 1) ^ w.i[1]) & 1);
-    const int z = w.i[2] + (((SLOT >> 2) ^ w.i[2]) & 1);
-    const float a = w.a[SLOT], s0 = w.s0[SLOT], s1 = w.s1[SLOT], s2 = w.s2[SLOT];
-    const float q = g4 * w.s3[SLOT];  // the auxiliary residual's sigma partial (0 when off)
-    float v[9] = {-a * rr[0], -a * rr[1], -a * rr[2], -(s0 * rr[0] + s1 * rr[1] + s2 * rr[2] + q * r4),
-                  a * a,      a * s0,     a * s1,     a * s2,
-                  s0 * s0 + s1 * s1 + s2 * s2 + q * q};
-    // Neighbouring rays hand over the same voxel at the same step, and their LDS atomics on one
-    // address serialise.  Fold the x neighbour's (lane ^ 1), the y neighbour's (lane ^ 8) and
-    // then lane ^ 2's product into this lane when the voxel is the same; the donor drops out.
-    // Straight-line code with every lane active (the swaps read the partner's registers).
-    const int lane = lane_id();
-    const int key = mine ? (z * G.ny + y) * G.nx + x : -1;
-    bool keep = mine;
-    auto fold = [&](auto swap, int bit) {
-        const int kc = keep ? key : -1;
-        const bool g = keep & (swap(kc) == kc);
-        const bool give = g & ((lane & bit) != 0);
-#pragma unroll
-        for (int c = 0; c < 9; ++c) v[c] += __int_as_float(swap(__float_as_int(give ? v[c] : 0.0f)));
-        keep = keep & !give;
-    };
-    fold([](int u) { return dpp_xor1(u); }, 1);
-    fold([](int u) { return dpp_row_xor8(u); }, 8);
-    fold([](int u) { return dpp_xor2(u); }, 2);
-    if (!keep) return;
-    const int lo[3] = {x, y, z};
-    if (B.inside(lo, lo)) B.add(x, y, z, v);
-    else sink((z * G.ny + y) * G.nx + x, v);
-}
-
-__device__ __forceinline__ void grad_flush(const Geo& G, unsigned pend, GradWin& w, const float rr[3], float r4,
-                                           float g4, BrickAtomic<9>& B, const SinkGrad& sink) {
-    grad_flush_slot<0>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<1>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<2>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<3>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<4>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<5>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<6>(G, pend, w, rr, r4, g4, B, sink);
-    grad_flush_slot<7>(G, pend, w, rr, r4, g4, B, sink);
-}
-
-__device__ __forceinline__ unsigned nonzero_slots(const GradWin& w) {
-    unsigned m = 0u;
-#pragma unroll
-    for (int b = 0; b < 8; ++b)
-        if (w.a[b] != 0.0f || w.s0[b] != 0.0f || w.s1[b] != 0.0f || w.s2[b] != 0.0f || w.s3[b] != 0.0f) m |= 1u << b;
-    return m;
-}
-
-__device__ __forceinline__ void clear_slots(GradWin& w, unsigned m) {
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        if (m & (1u << b)) {
-            w.a[b] = 0.0f; w.s0[b] = 0.0f; w.s1[b] = 0.0f; w.s2[b] = 0.0f; w.s3[b] = 0.0f;
-        }
-    }
-}
-
-template <int PD>
+template <int PD, bool SPLIT>
 __device__ __forceinline__ void grad_scatter(const Geo& G, const Ray& r, bool live, XL<PD> X, const float rr[3],
-                                             float r4, float g4, Depth depth, BrickAtomic<9>& B, TexTable<9>& TT,
-                                             float* __restrict__ grad,
-                                             float* __restrict__ blocks) {
+                                             float r4, float g4, Depth depth, GradBrick& B, TexTable<9>& TT,
+                                             float* __restrict__ grad, float* __restrict__ blocks) {
     SinkGrad sink{grad, blocks};
     const float Tx = exp_neg(depth.value());
     float S[3] = {0.0f, 0.0f, 0.0f};
-    if (live) {
-        // environment layers (the four texels of one lookup are distinct units)
-        auto emit = [&](const Tex& tx, const float c[3], float al, float Tl, const float Sb[3]) {
-            const float A = Tl * al;
-            const float d0 = Tl * (c[0] - Sb[0]), d1 = Tl * (c[1] - Sb[1]), d2 = Tl * (c[2] - Sb[2]);
+    // environment layers (the four texels of one lookup are distinct units)
+    auto emit = [&](const Tex& tx, const float c[3], float al, float Tl, const float Sb[3]) {
+        const float A = Tl * al;
+        const float d0 = Tl * (c[0] - Sb[0]), d1 = Tl * (c[1] - Sb[1]), d2 = Tl * (c[2] - Sb[2]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float w = tx.w[j];
-                const float a = w * A, s0 = w * d0, s1 = w * d1, s2 = w * d2;
-                if (a == 0.0f && s0 == 0.0f && s1 == 0.0f && s2 == 0.0f) continue;
-                const float v[9] = {-a * rr[0], -a * rr[1], -a * rr[2], -(s0 * rr[0] + s1 * rr[1] + s2 * rr[2]),
-                                    a * a,      a * s0,     a * s1,     a * s2,
-                                    s0 * s0 + s1 * s1 + s2 * s2};
-                TT.insert(tx.t[j], v, sink);
-            }
-        };
-        env_back<PD>(G, r, X, Tx, S, emit);
-    }
+        for (int j = 0; j < 4; ++j) {
+            const float w = tx.w[j];
+            const float a = w * A, s0 = w * d0, s1 = w * d1, s2 = w * d2;
+            if (a == 0.0f && s0 == 0.0f && s1 == 0.0f && s2 == 0.0f) continue;
+            const float v[9] = {-a * rr[0], -a * rr[1], -a * rr[2], -(s0 * rr[0] + s1 * rr[1] + s2 * rr[2]),
+                                a * a,      a * s0,     a * s1,     a * s2,
+                                s0 * s0 + s1 * s1 + s2 * s2};
+            TT.insert(tx.t[j], v, sink);
+        }
+    };
+    if constexpr (SPLIT) env_back4<PD>(G, r, live, X, Tx, S, emit);
+    else if (live) env_back<PD>(G, r, X, Tx, S, emit);
     TT.flush(sink);
-    B.clear_head(64);  // the table's keys (its sums are left at zero by the flush)
-    GradWin w;
-    w.i[0] = w.i[1] = w.i[2] = 0;
-    clear_slots(w, 0xFFu);
+    constexpr int NP = SPLIT ? 1 : 2;     // parities of x and y that a lane holds
+    constexpr int NS = 2 * NP * NP;       // slots: ((z parity) * NP + y) * NP + x
+    const int t = SPLIT ? slot_id() : 0;
+    GradWin<NS> w;
+    auto clear = [&](int n) { w.a[n] = w.s0[n] = w.s1[n] = w.s2[n] = w.s3[n] = 0.0f; };
+#pragma unroll
+    for (int n = 0; n < NS; ++n) clear(n);
+    int cx[NP], cy[NP], cz[2];  // coordinates of the window's voxels per parity
+#pragma unroll
+    for (int i = 0; i < NP; ++i) cx[i] = cy[i] = 0;
+    cz[0] = cz[1] = 0;
     bool started = false;  // the window holds this ray's sums
     bool ended = false;    // the ray's last sample is in the window, to be flushed whole
+    bool seen = false;     // a sample so far had a partial that is not zero
     // G_k from the back, starting with the environment seen from the grid exit
     float G0 = Tx * S[0], G1 = Tx * S[1], G2 = Tx * S[2];
     float Tn = Tx;
@@ -1548,80 +1500,160 @@ __device__ __forceinline__ void grad_scatter(const Geo& G, const Ray& r, bool li
     const float t_max = wave_max_f(r.K > 0 ? r.tf : -INFINITY);
     const int off = r.K > 0 ? (int)((t_max - r.tf) / unit + 0.5f) : 0;
     const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
-    for (int j = 0; j < J; ++j) {
+    // one step more than the samples, to flush the windows of the rays that end last
+    for (int j = 0; j <= J; ++j) {
         const int m = j - off;
         const bool on = m >= 0 && m < r.K;
         const int k = r.K - 1 - m;
-        Corners c;
+        Corners c{};
         float dk = 0.0f;
-        int lo[3] = {w.i[0], w.i[1], w.i[2]}, hi[3] = {w.i[0] + 1, w.i[1] + 1, w.i[2] + 1};
         if (on) {
             float g[3];
             dk = sample_at(G, r, k, g);
             corners(G, g, c);
+        }
+        // coordinate and weight of parity i along axis a
+        auto coord = [&](int a, int i) { return c.i[a] + ((c.i[a] ^ i) & 1); };
+        auto weight = [&](int a, int i) { return ((c.i[a] ^ i) & 1) ? c.f[a] : 1.0f - c.f[a]; };
+        int ex[NP], ey[NP], ez[2];
+        float wx[NP], wy[NP], wz[2];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                // cover the voxels about to leave the lane's window as well as the new ones
-                const int prev = started ? w.i[a] : c.i[a];
-                lo[a] = min(prev, c.i[a]);
-                hi[a] = max(prev, c.i[a]) + 1;
+        for (int i = 0; i < NP; ++i) {
+            ex[i] = coord(0, SPLIT ? t & 1 : i);
+            wx[i] = weight(0, SPLIT ? t & 1 : i);
+            ey[i] = coord(1, SPLIT ? t >> 1 : i);
+            wy[i] = weight(1, SPLIT ? t >> 1 : i);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            ez[i] = coord(2, i);
+            wz[i] = weight(2, i);
+        }
+        // the sample, first of all: the loads return while the window is flushed
+        float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        typename XL<PD>::Raw raw[2];
+        if constexpr (SPLIT) {
+            raw[0] = raw[1] = typename XL<PD>::Raw{};
+            if (on) {
+                const int u = ey[0] * nx + ex[0];
+                raw[0] = X.raw(u + ez[0] * nxy);
+                raw[1] = X.raw(u + ez[1] * nxy);
             }
         }
-        B.fit(G, on || ended, lo, hi, sink);
-        unsigned pend = 0u;
-        if (ended) pend = 0xFFu;
-        else if (on && started) pend = leaving_slots(w.i, c.i);
-        if (pend) pend &= nonzero_slots(w);
-        grad_flush(G, pend, w, rr, r4, g4, B, sink);
-        if (ended) {
-            clear_slots(w, 0xFFu);
-            ended = false;
-            started = false;
+        // masks of the lanes whose voxel of a parity changes (every voxel of a ray that has ended)
+        unsigned long long hx[NP], hy[NP], hz[2];
+        const unsigned long long move = __ballot(on && started && seen), end = __ballot(ended && seen);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            hx[i] = (__ballot(ex[i] != cx[i]) & move) | end;
+            hy[i] = __ballot(ey[i] != cy[i]) & move;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) hz[i] = __ballot(ez[i] != cz[i]) & move;
+        const unsigned long long any = hx[0] | hx[NP - 1] | hy[0] | hy[NP - 1] | hz[0] | hz[1];
+        if (any) {
+            int lo[3], hi[3];
+            lo[0] = min(cx[0], cx[NP - 1]), hi[0] = max(cx[0], cx[NP - 1]);
+            lo[1] = min(cy[0], cy[NP - 1]), hi[1] = max(cy[0], cy[NP - 1]);
+            lo[2] = min(cz[0], cz[1]), hi[2] = max(cz[0], cz[1]);
+            B.fit(G, __builtin_amdgcn_inverse_ballot_w64(any), lo, hi, sink);
+            int rx[NP], ry[NP], rz[2];
+            unsigned long long ix[NP], iy[NP], iz[2];
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                rx[i] = B.template at<0>(cx[i]);
+                ix[i] = __ballot(B.inside(0, cx[i]));
+                ry[i] = B.template at<1>(cy[i]);
+                iy[i] = __ballot(B.inside(1, cy[i]));
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                rz[i] = B.template at<2>(cz[i]);
+                iz[i] = __ballot(B.inside(2, cz[i]));
+            }
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+                const int px = n % NP, py = (n / NP) % NP, pz = n / (NP * NP);
+                const unsigned long long gone = hx[px] | hy[py] | hz[pz];
+                if (!gone) continue;
+                const unsigned long long in = gone & ix[px] & iy[py] & iz[pz];
+                const float a = w.a[n], s0 = w.s0[n], s1 = w.s1[n], s2 = w.s2[n];
+                const float z = g4 * w.s3[n];  // the auxiliary residual's sigma partial (0 when off)
+                float v[9] = {-a * rr[0], -a * rr[1], -a * rr[2],
+                              -(s0 * rr[0] + s1 * rr[1] + s2 * rr[2] + z * r4),
+                              a * a,      a * s0,     a * s1,     a * s2,
+                              s0 * s0 + s1 * s1 + s2 * s2 + z * z};
+                if (__builtin_amdgcn_inverse_ballot_w64(gone)) clear(n);
+                if (gone & ~in) {
+                    if (__builtin_amdgcn_inverse_ballot_w64(gone & ~in)) sink((cz[pz] * G.ny + cy[py]) * G.nx + cx[px], v);
+                }
+                const int at = rx[px] + ry[py] + rz[pz];
+                unsigned long long left = in;
+                if constexpr (!SPLIT) {
+                    // lanes of one voxel: the products of lane ^ 1, lane ^ 8 (the y neighbour) and
+                    // lane ^ 2 are added first, so that fewer lanes share an address
+                    grad_fold<0xB1>(at, v, left, 0x5555555555555555ull);
+                    grad_fold<0x128>(at, v, left, 0x00ff00ff00ff00ffull);
+                    grad_fold<0x4E>(at, v, left, 0x3333333333333333ull);
+                }
+                if (__builtin_amdgcn_inverse_ballot_w64(left)) B.add(at, v);
+            }
+        }
+        started = started && !ended;
+        ended = false;
+        if constexpr (SPLIT) {
+            const float4 q0 = XL<PD>::value(raw[0]), q1 = XL<PD>::value(raw[1]);
+            const float wxy = wx[0] * wy[0], w0 = wxy * wz[0], w1 = wxy * wz[1];
+            q.x = slot_sum(w0 * q0.x + w1 * q1.x);
+            q.y = slot_sum(w0 * q0.y + w1 * q1.y);
+            q.z = slot_sum(w0 * q0.z + w1 * q1.z);
+            q.w = slot_sum(w0 * q0.w + w1 * q1.w);
         }
         if (!on) continue;
-        if (started) clear_slots(w, leaving_slots(w.i, c.i));
-        w.i[0] = c.i[0]; w.i[1] = c.i[1]; w.i[2] = c.i[2];
+        float wn[NS];
+#pragma unroll
+        for (int n = 0; n < NS; ++n) wn[n] = wx[n % NP] * wy[(n / NP) % NP] * wz[n / (NP * NP)];
+        if constexpr (!SPLIT) {
+            const int uy[2] = {ey[0] * nx, ey[NP - 1] * nx}, uz[2] = {ez[0] * nxy, ez[1] * nxy};
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+                const float4 v = X(ex[n % NP] + (uy[(n / NP) % NP] + uz[n / (NP * NP)]));
+                q.x += wn[n] * v.x;
+                q.y += wn[n] * v.y;
+                q.z += wn[n] * v.z;
+                q.w += wn[n] * v.w;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            cx[i] = ex[i];
+            cy[i] = ey[i];
+        }
+        cz[0] = ez[0];
+        cz[1] = ez[1];
         started = true;
-        float sg, c0, c1, c2;
-        gather<PD>(X, c, nx, nxy, sg, c0, c1, c2);
-        const float tau = sg * dk;
+        const float tau = q.w * dk;
         depth.add(-tau);
         const float T = (k == 0) ? 1.0f : exp_neg(depth.value());
         const float al = one_minus_exp_neg(tau, exp_neg(tau));
         const float A = T * al;
-        const float ds0 = dk * (Tn * c0 - G0);
-        const float ds1 = dk * (Tn * c1 - G1);
-        const float ds2 = dk * (Tn * c2 - G2);
-        G0 += A * c0;
-        G1 += A * c1;
-        G2 += A * c2;
+        const float ds0 = dk * (Tn * q.x - G0);
+        const float ds1 = dk * (Tn * q.y - G1);
+        const float ds2 = dk * (Tn * q.z - G2);
+        G0 += A * q.x;
+        G1 += A * q.y;
+        G2 += A * q.z;
         Tn = T;
-        // slot b holds the corner whose offset along axis a is bit a of b xor the parity of
-        // c.i[a]: its weight is the product of the per-axis weights
-        float gw[3][2];
+        seen = seen || A != 0.0f || ds0 != 0.0f || ds1 != 0.0f || ds2 != 0.0f || g4 != 0.0f;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const bool odd = c.i[a] & 1;
-            gw[a][0] = odd ? c.f[a] : 1.0f - c.f[a];
-            gw[a][1] = odd ? 1.0f - c.f[a] : c.f[a];
-        }
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const float wb = gw[0][b & 1] * gw[1][(b >> 1) & 1] * gw[2][b >> 2];
-            w.a[b] += wb * A;
-            w.s0[b] += wb * ds0;
-            w.s1[b] += wb * ds1;
-            w.s2[b] += wb * ds2;
-            w.s3[b] += wb * dk;
+        for (int n = 0; n < NS; ++n) {
+            w.a[n] += wn[n] * A;
+            w.s0[n] += wn[n] * ds0;
+            w.s1[n] += wn[n] * ds1;
+            w.s2[n] += wn[n] * ds2;
+            w.s3[n] += wn[n] * dk;
         }
         if (k == 0) ended = true;
-    }
-    // rays whose last sample came in the final step
-    {
-        const int lo[3] = {w.i[0], w.i[1], w.i[2]}, hi[3] = {w.i[0] + 1, w.i[1] + 1, w.i[2] + 1};
-        B.fit(G, ended, lo, hi, sink);
-        unsigned pend = ended ? nonzero_slots(w) : 0u;
-        grad_flush(G, pend, w, rr, r4, g4, B, sink);
     }
     B.flush_all(G, sink);
 }
@@ -1686,15 +1718,25 @@ template <int MODE>
 struct Lds {
     static constexpr int NCH = MODE == M_GRAD ? 9 : 4;
     static constexpr bool SCATTER = MODE == M_VJP || MODE == M_JTJ || MODE == M_GRAD;
-    static constexpr int WAVES = (MODE == M_VJP || MODE == M_JTJ) ? 4 : 1;  // waves per SIMD to leave registers for
+    static constexpr int WAVES = (MODE == M_VJP || MODE == M_JTJ) ? 4 : MODE == M_GRAD ? 3 : 1;  // waves per SIMD to leave registers for
 };
 
-template <int MODE, int PD, bool SPLIT>
+// How many lanes march a ray.
+enum Split {
+    S_ONE = 0,   // one lane
+    S_FOUR = 1,  // four lanes, forward4 and adjoint4
+    S_BACK = 2   // gradient pass only: the four lanes of a ray all run the one-lane forward march and
+                 // share the way back.  A scene's residuals come from one kind of forward march (the render
+                 // pass's) in every pass, so that they agree to the last bit.
+};
+
+template <int MODE, int PD, int KIND>
 __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs A) {
     constexpr int NCH = Lds<MODE>::NCH;
     constexpr bool SCATTER = Lds<MODE>::SCATTER;
     constexpr bool JT = MODE == M_VJP || MODE == M_JTJ;
-    __shared__ f4 s_brick[(SCATTER && !JT) ? kWaves * NCH * kB3 / 4 : 1];
+    constexpr bool SPLIT = KIND != S_ONE;
+    __shared__ double s_brick[MODE == M_GRAD ? kWaves * NCH * GradBrick::kW3 : 1];
     __shared__ f4 s_brick4[JT ? kWaves * kB3 : 1];
     __shared__ f4 s_stage[JT ? kWaves * kStageRow : 1];
     if (A.done && *A.done) return;
@@ -1715,11 +1757,11 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
     if constexpr (MODE == M_JVP || MODE == M_JTJ) {
         VecF4 V;
         V.r = make_rsrc(A.v, (unsigned)units * VecF4::kBytes);
-        if constexpr (SPLIT) forward4<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f);
+        if constexpr (KIND == S_FOUR) forward4<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f);
         else forward<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth);
     } else {
         const float thresh = MODE == M_RENDER ? A.thresh : 0.0f;
-        if constexpr (SPLIT) forward4<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
+        if constexpr (KIND == S_FOUR) forward4<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
         else forward<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
     }
     // auxiliary opacity residual (Sec. III-I, Eq. 10): r4 = lambda (1 - 4 (T - 1/2)^2) =
@@ -1757,12 +1799,13 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
         }
     } else if constexpr (SCATTER) {
         // the texel hash table of each pass borrows the head of its window's storage until it
-        // is flushed (keys: 64 ints, then NCH x 64 sums)
+        // is flushed
         TexTable<NCH> TT;
         if constexpr (JT) {
             Brick4 B;
             B.init(s_brick4 + wave * kB3, (float*)(s_stage + wave * kStageRow));
-            TT.init((int*)(s_brick4 + wave * kB3), (float*)(s_brick4 + wave * kB3 + 16));
+            static_assert(TexTable<NCH>::kDoubles * sizeof(double) <= kB3 * sizeof(f4), "the table fits the window");
+            TT.init((double*)(s_brick4 + wave * kB3));
             float u[3] = {0.0f, 0.0f, 0.0f};
             float u4 = 0.0f;
             if (p.active) {
@@ -1784,21 +1827,22 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
             if constexpr (SPLIT) adjoint4<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
             else adjoint_scatter<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
         } else {
-            BrickAtomic<NCH> B;
-            B.init((float*)(s_brick + wave * NCH * kB3 / 4));
-            TT.init((int*)(s_brick + wave * NCH * kB3 / 4), (float*)(s_brick + wave * NCH * kB3 / 4) + 64);
+            static_assert(NCH == GradBrick::kCh && TexTable<NCH>::kDoubles <= NCH * GradBrick::kW3, "the table fits the window");
+            GradBrick B;
+            B.init(s_brick + wave * NCH * GradBrick::kW3, r.gd);
+            TT.init(s_brick + wave * NCH * GradBrick::kW3);
             float res[3] = {0.0f, 0.0f, 0.0f};
             if (p.active && A.targets) {
 #pragma unroll
                 for (int ch = 0; ch < 3; ++ch) {
                     res[ch] = H[ch] - A.targets[3 * p.ray + ch];
-                    rr_sum += (double)res[ch] * (double)res[ch];
+                    if (first) rr_sum += (double)res[ch] * (double)res[ch];
                 }
-                rr_sum += (double)r4 * (double)r4;
+                if (first) rr_sum += (double)r4 * (double)r4;
             }
             // the auxiliary residual's row: d r4 / d sigma_k = g4 delta_k
             const float g4 = -dr4 * Texit;
-            grad_scatter<PD>(G, r, p.active, X, res, p.active ? r4 : 0.0f, g4, depth, B, TT, A.y, A.blocks);
+            grad_scatter<PD, SPLIT>(G, r, p.active, X, res, p.active ? r4 : 0.0f, g4, depth, B, TT, A.y, A.blocks);
         }
     }
     if constexpr (MODE == M_RENDER || MODE == M_GRAD) {
@@ -1862,22 +1906,24 @@ __global__ __launch_bounds__(kBlock) void k_footprint(Geo G, const DevCam* cams,
     }
 }
 
-template <int MODE, int PD, bool SPLIT>
+template <int MODE, int PD, int KIND>
 hipError_t launch_one(const Geo& g, const RayArgs& a, hipStream_t st) {
-    const unsigned grid = (unsigned)ray_blocks(g, SPLIT);
+    const unsigned grid = (unsigned)ray_blocks(g, KIND != S_ONE);
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_ray<MODE, PD, SPLIT>), dim3(grid), dim3(kBlock), 0, st, g, a);
+    hipLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), dim3(kBlock), 0, st, g, a);
     return hipGetLastError();
 }
 
-template <int PD, bool SPLIT>
+template <int PD, int KIND>
 hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st) {
     switch (mode) {
-        case M_RENDER: return launch_one<M_RENDER, PD, SPLIT>(g, a, st);
-        case M_JVP: return launch_one<M_JVP, PD, SPLIT>(g, a, st);
-        case M_VJP: return launch_one<M_VJP, PD, SPLIT>(g, a, st);
-        case M_JTJ: return launch_one<M_JTJ, PD, SPLIT>(g, a, st);
-        case M_GRAD: return launch_one<M_GRAD, PD, false>(g, a, st);
+        case M_RENDER: return launch_one<M_RENDER, PD, KIND>(g, a, st);
+        case M_JVP: return launch_one<M_JVP, PD, KIND>(g, a, st);
+        case M_VJP: return launch_one<M_VJP, PD, KIND>(g, a, st);
+        case M_JTJ: return launch_one<M_JTJ, PD, KIND>(g, a, st);
+        case M_GRAD:
+            if (KIND == S_FOUR && !split_rays(M_RENDER, g)) return launch_one<M_GRAD, PD, S_BACK>(g, a, st);
+            return launch_one<M_GRAD, PD, KIND>(g, a, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1889,13 +1935,25 @@ int64_t ray_blocks(const Geo& g, bool split) {
     return (int64_t)g.n_cams * ((g.width + w - 1) / w) * ((g.height + h - 1) / h);
 }
 
-bool split_rays(int mode, const Geo& g) { return mode != M_GRAD && ray_blocks(g, false) < 2048; }
+// Four lanes per ray where there are too few rays to fill the chip, and, in the passes that scatter,
+// where pixels are so wide (in voxels) that the windows of an 8x8 tile cannot hold its rays.
+// Measured at 128^3, one lane / four lanes per ray:
+//   J^T J v    400x400 images (0.47 voxels a pixel): 2500 workgroups 1.75 / 1.50 ms, 5000 2.50 / 2.60;
+//              16 images of 340x340 (0.55) 6.4 / 7.5 ms, 300x300 (0.62) 6.3 / 6.0, 256x256 (0.73) 10.7 / 6.7
+//   gradient   400x400: 1250 workgroups 1.74 / 1.62 ms, 2500 3.43 / 3.38, 5000 5.1 / 6.1;
+//              340x340 14.9 / 17.9 ms, 300x300 20.4 / 13.8, 256x256 34 / 15 (S_FOUR)
+//   residuals  400x400: 1250 workgroups 0.21 / 0.16 ms, 2500 0.31 / 0.31, 5000 0.47 / 0.57 at any width
+bool split_rays(int mode, const Geo& g) {
+    const bool scatter = mode == M_VJP || mode == M_JTJ || mode == M_GRAD;
+    const int64_t few = mode == M_VJP || mode == M_JTJ ? 3500 : mode == M_GRAD ? 2000 : 1800;
+    return ray_blocks(g, false) < few || (scatter && g.pitch > 0.6f);
+}
 
 hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st) {
     const bool split = split_rays(mode, g);
     if (param_dtype == PERF_BF16)
-        return split ? launch_mode<PERF_BF16, true>(mode, g, a, st) : launch_mode<PERF_BF16, false>(mode, g, a, st);
-    return split ? launch_mode<PERF_F32, true>(mode, g, a, st) : launch_mode<PERF_F32, false>(mode, g, a, st);
+        return split ? launch_mode<PERF_BF16, S_FOUR>(mode, g, a, st) : launch_mode<PERF_BF16, S_ONE>(mode, g, a, st);
+    return split ? launch_mode<PERF_F32, S_FOUR>(mode, g, a, st) : launch_mode<PERF_F32, S_ONE>(mode, g, a, st);
 }
 
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,
