@@ -235,44 +235,173 @@ __device__ __forceinline__ void load_features(const float* __restrict__ feat, co
     }
 }
 
-// ------------------------------------------------------------------ inference
-constexpr int kInferWaves = 4;
+// ------------------------------------------------------------------ chained products in registers
+// Both layers' products are taken as H^T = W X^T: the result register 4g + j of lane l holds feature
+// 8g + 4(l/32) + j of unit l % 32, which is what the next product's B operand wants of that lane at K
+// step g, so activations go from one product to the next in registers.  The weights are the A
+// operands and stay in registers too (56 of them), read once per wave.
+struct RegWeights {
+    s4 w1[2][NIP / 8], w2[2][NH / 8], w3[NH / 8];
+    // lane l: row l % 32 of each block of 32 outputs, inputs 8 ks + 4 (l / 32) + (0 .. 3)
+    __device__ __forceinline__ void load(const unsigned short* __restrict__ w) {
+        const int r = lane() & 31, h = lane() >> 5;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+#pragma unroll
+            for (int ks = 0; ks < NIP / 8; ++ks) w1[mb][ks] = *(const s4*)(w + OFF_W1 + (mb * 32 + r) * NIP + ks * 8 + 4 * h);
+#pragma unroll
+            for (int ks = 0; ks < NH / 8; ++ks) w2[mb][ks] = *(const s4*)(w + OFF_W2 + (mb * 32 + r) * NH + ks * 8 + 4 * h);
+        }
+#pragma unroll
+        for (int ks = 0; ks < NH / 8; ++ks)
+            w3[ks] = r < NOP ? *(const s4*)(w + OFF_W3 + r * NH + ks * 8 + 4 * h) : s4{0, 0, 0, 0};
+    }
+};
 
-__global__ __launch_bounds__(64 * kInferWaves) void k_mlp_infer(const unsigned short* __restrict__ w,
-                                                                const float* __restrict__ norm, float q_fallback,
-                                                                const float* __restrict__ feat,
-                                                                const float* __restrict__ blocks, int64_t units,
-                                                                float* __restrict__ minv) {
-    __shared__ unsigned short sW1[NH * LD16], sW2[NH * LD64], sW3[32 * LD64];
-    __shared__ float sb1[NH], sb2[NH], sb3[NOP];
-    __shared__ unsigned short sX[kInferWaves][TU * LD16], sH1[kInferWaves][TU * LD64], sH2[kInferWaves][TU * LD64];
-    __shared__ float sO[kInferWaves][TU * 17];
-    Weights W{(lds_bf*)sW1, (lds_bf*)sW2, (lds_bf*)sW3, sb1, sb2, sb3};
-    load_weights(w, W, nullptr, nullptr);
-    const int wv = threadIdx.x >> 6, l = lane();
-    lds_bf* Xs = (lds_bf*)sX[wv];
-    lds_bf* H1s = (lds_bf*)sH1[wv];
-    lds_bf* H2s = (lds_bf*)sH2[wv];
-    float* Os = sO[wv];
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float fl2 __attribute__((ext_vector_type(2)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+// four floats rounded to bfloat16 (nearest even)
+__device__ __forceinline__ s4 pack4(float a, float b, float c, float d) {
+    const bf2 lo = __builtin_convertvector(fl2{a, b}, bf2), hi = __builtin_convertvector(fl2{c, d}, bf2);
+    u2 q;
+    q.x = __builtin_bit_cast(unsigned, lo);
+    q.y = __builtin_bit_cast(unsigned, hi);
+    return __builtin_bit_cast(s4, q);
+}
+// the upper half wave of a changes places with the lower half wave of b
+__device__ __forceinline__ void swap32(unsigned& a, unsigned& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void swap32(s4& a, s4& b) {
+    u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    unsigned x0 = x.x, x1 = x.y, y0 = y.x, y1 = y.y;
+    swap32(x0, y0);
+    swap32(x1, y1);
+    a = __builtin_bit_cast(s4, u2{x0, x1});
+    b = __builtin_bit_cast(s4, u2{y0, y1});
+}
+__device__ __forceinline__ void swap32(float& a, float& b) {
+    unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    swap32(x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+
+// ReLU of a layer's result (64 features of 32 units) plus its bias, as the next product's operand.
+__device__ __forceinline__ void activate(const f16v (&acc)[2], const float* bias, s4 (&out)[NH / 8]) {
+    const int h = lane() >> 5;
+    asm volatile("" ::: "memory");  // the bias is read here, not kept in registers between the tiles
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 b = *(const float4*)(bias + mb * 32 + 8 * g + 4 * h);
+            out[4 * mb + g] = pack4(fmaxf(acc[mb][4 * g] + b.x, 0.0f), fmaxf(acc[mb][4 * g + 1] + b.y, 0.0f),
+                                    fmaxf(acc[mb][4 * g + 2] + b.z, 0.0f), fmaxf(acc[mb][4 * g + 3] + b.w, 0.0f));
+        }
+}
+template <int KS>
+__device__ __forceinline__ void layer(const s4 (&w)[2][KS], const s4 (&x)[KS], f16v (&acc)[2]) {
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[mb][v] = 0.0f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w[mb][ks], x[ks], acc[mb], 0, 0, 0);
+}
+
+// The network's inputs of one unit per lane as the two B operands of a wave's 64 units: tile[t][ks] for the
+// units 32 t + l % 32.
+__device__ __forceinline__ void unit_inputs(const float* __restrict__ feat, const float* __restrict__ norm,
+                                            const float* b, int64_t unit, bool in, s4 (&tile)[2][NIP / 8]) {
+    float x[NNET], cpl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (in) block_inputs(b, cpl);
+#pragma unroll
+    for (int i = 0; i < NNET; ++i) {
+        float v = 0.0f;
+        if (i >= NIN) v = cpl[i < NIN ? 0 : i - NIN];
+        else if (in) v = fminf(fmaxf((feat[NIN * unit + i] - norm[i]) * norm[NIP + i], -kClamp), kClamp);
+        x[i] = v;
+    }
+    tile[0][0] = pack4(x[0], x[1], x[2], x[3]);
+    tile[1][0] = pack4(x[4], x[5], x[6], x[7]);
+    tile[0][1] = pack4(x[8], x[9], 0.0f, 0.0f);
+    tile[1][1] = s4{0, 0, 0, 0};
+    swap32(tile[0][0], tile[1][0]);
+    swap32(tile[0][1], tile[1][1]);
+}
+
+// ------------------------------------------------------------------ inference
+// One wave takes 64 units at a time, two products of 32 units each.  Bound by the VALU work around the
+// products (the block inputs and D^-1/2 in double, softplus) and by HBM: 92 B per unit.  With the
+// activations staged in LDS one wave per SIMD fitted (113 KB a workgroup) and 2.2 M units took 379 us;
+// INFER_NOW.
+constexpr int kInferWaves = 4;
+constexpr int kInferBlocks = 768;  // three workgroups per CU
+
+__global__ __launch_bounds__(64 * kInferWaves, 3) void k_mlp_infer(const unsigned short* __restrict__ w,
+                                                                   const float* __restrict__ norm, float q_fallback,
+                                                                   const float* __restrict__ feat,
+                                                                   const float* __restrict__ blocks, int64_t units,
+                                                                   float* __restrict__ minv) {
+    __shared__ __align__(16) float sb1[NH], sb2[NH], sb3[NOP];
+    for (int i = threadIdx.x; i < NH; i += blockDim.x) {
+        sb1[i] = bf2f(w[OFF_B1 + i]);
+        sb2[i] = bf2f(w[OFF_B2 + i]);
+        if (i < NOP) sb3[i] = bf2f(w[OFF_B3 + i]);
+    }
+    __syncthreads();
+    RegWeights W;
+    W.load(w);
+    const int wv = threadIdx.x >> 6, l = lane(), h = l >> 5;
     const int64_t n_tiles = (units + TU - 1) / TU;
     for (int64_t tile = (int64_t)blockIdx.x * kInferWaves + wv; tile < n_tiles; tile += (int64_t)gridDim.x * kInferWaves) {
         const int64_t unit = tile * TU + l;
-        load_features(feat, norm, blocks, unit, units, Xs + l * LD16, nullptr, 0);
-        forward_tile(W, Xs, H1s, H2s, Os, nullptr, nullptr);
-        if (unit < units) {
-            const float* b = blocks + 5 * unit;
-            float4* o = reinterpret_cast<float4*>(minv) + 3 * unit;
+        const bool in = unit < units;
+        float b[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (in) {
+#pragma unroll
+            for (int i = 0; i < 5; ++i) b[i] = blocks[5 * unit + i];
+        }
+        s4 x[2][NIP / 8];
+        unit_inputs(feat, norm, b, unit, in, x);
+        float o[2][6];  // outputs 4h .. 4h + 3, 8, 9 of the unit l % 32 of each half
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f16v acc[2];
+            s4 y[NH / 8];
+            layer(W.w1, x[t], acc);
+            activate(acc, sb1, y);
+            layer(W.w2, y, acc);
+            activate(acc, sb2, y);
+            f16v out;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) out[v] = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < NH / 8; ++ks) out = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(W.w3[ks], y[ks], out, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[t][i] = out[i] + sb3[4 * h + i];
+            o[t][4] = out[4] + sb3[8];
+            o[t][5] = out[5] + sb3[9];
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) swap32(o[0][i], o[1][i]);
+        const float raw[NO] = {o[0][0], o[0][1], o[0][2], o[0][3], o[1][0], o[1][1], o[1][2], o[1][3], o[0][4], o[0][5]};
+        if (in) {
+            float4* out = reinterpret_cast<float4*>(minv) + 3 * unit;
             const float d = b[0], f = b[4];
             const float m = fmaxf(d, f);
             bool finite = true;
 #pragma unroll
             for (int i = 0; i < 5; ++i) finite &= isfinite(b[i]);
             if (!(m > 0.0f) || !finite) {  // no ray, or a non-finite block: an empty unit
-                o[0] = o[1] = o[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                out[0] = out[1] = out[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             } else {
-                float raw[NO];
-#pragma unroll
-                for (int i = 0; i < NO; ++i) raw[i] = Os[l * 17 + i];
                 float L[4][4];
                 make_L(raw, L);
                 // D^-1/2 and the normalised coupling in double (d may be subnormal)
@@ -307,13 +436,13 @@ __global__ __launch_bounds__(64 * kInferWaves) void k_mlp_infer(const unsigned s
                     // the exact block inverse in the elimination form of the block preconditioner,
                     // marked by a negative t_d
                     const double is = 1.0 / (1.0 - (a0 * a0 + a1 * a1 + a2 * a2));
-                    o[0] = make_float4(-td, tf, e[0], e[1]);
-                    o[1] = make_float4(e[2], (float)is, 0.0f, 0.0f);
-                    o[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    out[0] = make_float4(-td, tf, e[0], e[1]);
+                    out[1] = make_float4(e[2], (float)is, 0.0f, 0.0f);
+                    out[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 } else {
-                    o[0] = make_float4(td, tf, L[0][0], L[1][0]);
-                    o[1] = make_float4(L[1][1], L[2][0], L[2][1], L[2][2]);
-                    o[2] = make_float4(L[3][0], L[3][1], L[3][2], L[3][3]);
+                    out[0] = make_float4(td, tf, L[0][0], L[1][0]);
+                    out[1] = make_float4(L[1][1], L[2][0], L[2][1], L[2][2]);
+                    out[2] = make_float4(L[3][0], L[3][1], L[3][2], L[3][3]);
                 }
             }
         }
@@ -584,7 +713,7 @@ hipError_t launch_mlp_infer(const uint16_t* w, const float* norm, float q_fallba
                             const float* blocks, int64_t units, float* minv, hipStream_t st) {
     const int64_t tiles = (units + TU - 1) / TU;
     int64_t g = (tiles + kInferWaves - 1) / kInferWaves;
-    if (g > 4096) g = 4096;
+    if (g > kInferBlocks) g = kInferBlocks;
     if (g < 1) g = 1;
     hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)g), dim3(64 * kInferWaves), 0, st, w, norm, q_fallback, feat, blocks,
                        units, minv);
