@@ -15,8 +15,8 @@
 // a unit whose prediction misses its own normalised block by q = ||L L^T B~ - I||_F^2 above a
 // threshold takes the exact block inverse instead (plain block-Jacobi as the fallback).
 //
-// Every product is C[M x N] = A[M x K] * Bt[N x K]^T with both operands bfloat16 in LDS,
-// K contiguous, rows padded to avoid bank conflicts.  One wave owns a tile of 64 units.
+// Every product is C[M x N] = A[M x K] * Bt[N x K]^T with both operands bfloat16 in registers.
+// One wave owns a tile of 64 units.
 // MFMA operand layout (checked on the device): lane l holds A[l%32][4(l/32)+j] and
 // B[4(l/32)+j][l%32], j < 4; result register v of lane l is C[8(v/4)+4(l/32)+v%4][l%32].
 #include "perf_internal.h"
@@ -28,10 +28,9 @@
 namespace perf {
 namespace {
 
+#define LDS __attribute__((address_space(3)))
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
-#define LDS __attribute__((address_space(3)))
-typedef LDS unsigned short lds_bf;
 
 constexpr int NIN = PERF_MLP_NFEAT, NIP = 16, NH = 64, NO = 10, NOP = 16;
 constexpr int NNET = NIN + 4;  // network inputs: the stored features, the block's coupling and its Schur log
@@ -40,7 +39,6 @@ constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NH * NIP, OFF_W2 = OFF_B1 + NH, OFF_
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NOP * NH, NW = OFF_B3 + NOP;
 static_assert(NW == PERF_MLP_NW, "packed weight layout");
 constexpr int TU = 64;   // units per wave tile
-constexpr int LD16 = 20, LD32 = 36, LD64 = 68;  // padded row strides (elements)
 constexpr float kRidge = 1e-6f;
 constexpr float kKappa = 4.0f;  // per-unit loss is quadratic up to ||E||^2 = kKappa, linear in ||E|| above
 constexpr float kClamp = 8.0f;  // standardised inputs are clamped to [-kClamp, kClamp]
@@ -53,121 +51,29 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
 __device__ __forceinline__ float bf2f(unsigned short b) { return __uint_as_float(((unsigned)b) << 16); }
 __device__ __forceinline__ int lane() { return threadIdx.x & 63; }
 
-// acc[mb][nb] += A[(mb*32+..) x K] * Bt[(nb*32+..) x K]^T
-template <int MB, int NB, int KS>
-__device__ __forceinline__ void wgemm(const lds_bf* A, int lda, const lds_bf* Bt, int ldb, f16v (&acc)[MB][NB]) {
-    const int r = lane() & 31, h = lane() >> 5;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        s4 a[MB], b[NB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) a[mb] = *(const LDS s4*)(A + (mb * 32 + r) * lda + ks * 8 + 4 * h);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) b[nb] = *(const LDS s4*)(Bt + (nb * 32 + r) * ldb + ks * 8 + 4 * h);
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[mb], b[nb], acc[mb][nb], 0, 0, 0);
-    }
+// log(1 + exp(x)) = max(x, 0) + log1p(e), e = exp(-|x|).  The exponential's argument is reduced in
+// two parts, and log1p(e) = 2 atanh(s), s = e / (2 + e) <= 1/3, by its series to s^15 (truncated below
+// 1e-8): relative error about 2e-7 everywhere, in some 25 instructions where expf and log1pf take 120.
+__device__ __forceinline__ float softplus(float x) {
+    const float a = fminf(fabsf(x), 100.0f);
+    const float t = -a * 1.44269502e+0f;
+    const float r = fmaf(-a, 1.44269502e+0f, -t) - a * 1.92596299e-8f;  // the rest of -a log2(e)
+    float e = __builtin_amdgcn_exp2f(t);
+    e = fmaf(e, r * 0.69314718f, e);
+    const float den = 2.0f + e;
+    const float y = __builtin_amdgcn_rcpf(den);
+    float s = e * y;
+    s = fmaf(fmaf(-s, den, e), y, s);
+    const float z = s * s;
+    float q = fmaf(z, 1.0f / 15.0f, 1.0f / 13.0f);
+    q = fmaf(q, z, 1.0f / 11.0f);
+    q = fmaf(q, z, 1.0f / 9.0f);
+    q = fmaf(q, z, 1.0f / 7.0f);
+    q = fmaf(q, z, 1.0f / 5.0f);
+    q = fmaf(q, z, 1.0f / 3.0f);
+    const float l = 2.0f * fmaf(s * z, q, s);
+    return x == x ? fmaxf(x, 0.0f) + l : x;
 }
-
-template <int MB, int NB>
-__device__ __forceinline__ void zero(f16v (&acc)[MB][NB]) {
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.0f;
-}
-
-// row / column of result register v of this lane in block (mb, nb)
-__device__ __forceinline__ int crow(int mb, int v) { return mb * 32 + 8 * (v >> 2) + 4 * (lane() >> 5) + (v & 3); }
-__device__ __forceinline__ int ccol(int nb) { return nb * 32 + (lane() & 31); }
-
-struct Weights {  // bfloat16 weights in LDS, rows K-contiguous
-    lds_bf* W1;   // [64][LD16]  (h, i)
-    lds_bf* W2;   // [64][LD64]  (h_out, h_in)
-    lds_bf* W3;   // [32][LD64]  (o, h), rows >= 16 zero
-    float* b1;
-    float* b2;
-    float* b3;
-};
-
-// Cooperative load of the packed bf16 weights (whole workgroup, then a barrier).
-__device__ void load_weights(const unsigned short* __restrict__ w, Weights W, lds_bf* W2t, lds_bf* W3t) {
-    for (int i = threadIdx.x; i < NH * NIP; i += blockDim.x) W.W1[(i / NIP) * LD16 + i % NIP] = w[OFF_W1 + i];
-    for (int i = threadIdx.x; i < NH * NH; i += blockDim.x) {
-        const int ho = i / NH, hi = i % NH;
-        W.W2[ho * LD64 + hi] = w[OFF_W2 + i];
-        if (W2t) W2t[hi * LD64 + ho] = w[OFF_W2 + i];
-    }
-    for (int i = threadIdx.x; i < 32 * NH; i += blockDim.x) {
-        const int o = i / NH, hh = i % NH;
-        const unsigned short v = o < NOP ? w[OFF_W3 + i] : (unsigned short)0;
-        W.W3[o * LD64 + hh] = v;
-        if (W3t) W3t[hh * LD32 + o] = v;
-    }
-    for (int i = threadIdx.x; i < NH; i += blockDim.x) {
-        W.b1[i] = bf2f(w[OFF_B1 + i]);
-        W.b2[i] = bf2f(w[OFF_B2 + i]);
-    }
-    for (int i = threadIdx.x; i < NOP; i += blockDim.x) W.b3[i] = bf2f(w[OFF_B3 + i]);
-    __syncthreads();
-}
-
-// Forward pass of one tile: X (bf16 [TU][LD16]) -> H1, H2 (bf16 [TU][LD64]) -> O (fp32 [TU][17]).
-// With Xt/H1t/H2t non-null the transposed activations ([feature][unit]) are written too.
-__device__ void forward_tile(const Weights& W, const lds_bf* Xs, lds_bf* H1s, lds_bf* H2s, float* Os, lds_bf* H1t,
-                             lds_bf* H2t) {
-    {
-        f16v acc[2][2];
-        zero(acc);
-        wgemm<2, 2, NIP / 8>(Xs, LD16, W.W1, LD16, acc);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int u = crow(mb, v), hh = ccol(nb);
-                    const unsigned short q = f2bf(fmaxf(acc[mb][nb][v] + W.b1[hh], 0.0f));
-                    H1s[u * LD64 + hh] = q;
-                    if (H1t) H1t[hh * LD64 + u] = q;
-                }
-    }
-    {
-        f16v acc[2][2];
-        zero(acc);
-        wgemm<2, 2, NH / 8>(H1s, LD64, W.W2, LD64, acc);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int u = crow(mb, v), hh = ccol(nb);
-                    const unsigned short q = f2bf(fmaxf(acc[mb][nb][v] + W.b2[hh], 0.0f));
-                    H2s[u * LD64 + hh] = q;
-                    if (H2t) H2t[hh * LD64 + u] = q;
-                }
-    }
-    {
-        f16v acc[2][1];
-        zero(acc);
-        wgemm<2, 1, NH / 8>(H2s, LD64, W.W3, LD64, acc);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int u = crow(mb, v), o = ccol(0);
-                if (o < NOP) Os[u * 17 + o] = acc[mb][0][v] + W.b3[o];
-            }
-    }
-}
-
-__device__ __forceinline__ float softplus(float x) { return x > 20.0f ? x : log1pf(expf(x)); }
 __device__ __forceinline__ float sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 // lower-triangular L from the 10 raw outputs, rows (0,0),(1,0),(1,1),(2,0),...,(3,3)
@@ -183,7 +89,6 @@ __device__ __forceinline__ void make_L(const float raw[NO], float L[4][4]) {
         for (int j = 0; j <= i; ++j, ++k) L[i][j] = (i == j) ? softplus(raw[k]) : raw[k];
 }
 
-// standardised features of one unit into the X tile row (bf16, zero padded): clamp((f - mu) s)
 // The block inputs of a unit's block [d, e (3), f]: the normalised colour-density coupling
 // e~ = e / sqrt((d + rho)(f + rho)) (|e~| < 1 for a positive semi-definite block), then
 // -1/2 log(1 - |e~|^2), the log of 1 / sqrt of the Schur complement of the normalised block (the
@@ -213,33 +118,12 @@ __device__ __forceinline__ void block_inputs(const float* __restrict__ b, float 
     e[3] = sc > exp(-2.0 * (double)kSchurCap) ? (float)(-0.5 * log(sc)) : kSchurCap;
 }
 
-// one unit's network inputs, rounded to bfloat16: its standardised stored features (clamped),
-// then the block inputs as they are, then zeros
-__device__ __forceinline__ void load_features(const float* __restrict__ feat, const float* __restrict__ norm,
-                                              const float* __restrict__ blocks, int64_t unit, int64_t n,
-                                              lds_bf* Xrow, lds_bf* Xt, int col) {
-    float cpl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (unit < n) block_inputs(blocks + 5 * unit, cpl);
-#pragma unroll
-    for (int i = 0; i < NIP; ++i) {
-        float v = 0.0f;
-        if (unit < n && i < NIN) v = fminf(fmaxf((feat[NIN * unit + i] - norm[i]) * norm[NIP + i], -kClamp), kClamp);
-        else if (unit < n && i < NNET) v = cpl[i - NIN];
-        const unsigned short q = f2bf(v);
-        Xrow[i] = q;
-        if (Xt) Xt[i * LD64 + col] = q;
-    }
-    if (Xt) {
-#pragma unroll
-        for (int i = NIP; i < 32; ++i) Xt[i * LD64 + col] = 0;
-    }
-}
-
 // ------------------------------------------------------------------ chained products in registers
 // Both layers' products are taken as H^T = W X^T: the result register 4g + j of lane l holds feature
 // 8g + 4(l/32) + j of unit l % 32, which is what the next product's B operand wants of that lane at K
 // step g, so activations go from one product to the next in registers.  The weights are the A
 // operands and stay in registers too (56 of them), read once per wave.
+typedef s4 s4u __attribute__((aligned(2)));  // four weights at any address
 struct RegWeights {
     s4 w1[2][NIP / 8], w2[2][NH / 8], w3[NH / 8];
     // lane l: row l % 32 of each block of 32 outputs, inputs 8 ks + 4 (l / 32) + (0 .. 3)
@@ -248,13 +132,13 @@ struct RegWeights {
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
 #pragma unroll
-            for (int ks = 0; ks < NIP / 8; ++ks) w1[mb][ks] = *(const s4*)(w + OFF_W1 + (mb * 32 + r) * NIP + ks * 8 + 4 * h);
+            for (int ks = 0; ks < NIP / 8; ++ks) w1[mb][ks] = *(const s4u*)(w + OFF_W1 + (mb * 32 + r) * NIP + ks * 8 + 4 * h);
 #pragma unroll
-            for (int ks = 0; ks < NH / 8; ++ks) w2[mb][ks] = *(const s4*)(w + OFF_W2 + (mb * 32 + r) * NH + ks * 8 + 4 * h);
+            for (int ks = 0; ks < NH / 8; ++ks) w2[mb][ks] = *(const s4u*)(w + OFF_W2 + (mb * 32 + r) * NH + ks * 8 + 4 * h);
         }
 #pragma unroll
         for (int ks = 0; ks < NH / 8; ++ks)
-            w3[ks] = r < NOP ? *(const s4*)(w + OFF_W3 + r * NH + ks * 8 + 4 * h) : s4{0, 0, 0, 0};
+            w3[ks] = r < NOP ? *(const s4u*)(w + OFF_W3 + r * NH + ks * 8 + 4 * h) : s4{0, 0, 0, 0};
     }
 };
 
@@ -315,11 +199,10 @@ __device__ __forceinline__ void layer(const s4 (&w)[2][KS], const s4 (&x)[KS], f
         for (int mb = 0; mb < 2; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(w[mb][ks], x[ks], acc[mb], 0, 0, 0);
 }
 
-// The network's inputs of one unit per lane as the two B operands of a wave's 64 units: tile[t][ks] for the
-// units 32 t + l % 32.
-__device__ __forceinline__ void unit_inputs(const float* __restrict__ feat, const float* __restrict__ norm,
-                                            const float* b, int64_t unit, bool in, s4 (&tile)[2][NIP / 8]) {
-    float x[NNET], cpl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+// The network's inputs of one unit.
+__device__ __forceinline__ void net_inputs(const float* __restrict__ feat, const float* __restrict__ norm,
+                                           const float* b, int64_t unit, bool in, float (&x)[NNET]) {
+    float cpl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (in) block_inputs(b, cpl);
 #pragma unroll
     for (int i = 0; i < NNET; ++i) {
@@ -328,6 +211,14 @@ __device__ __forceinline__ void unit_inputs(const float* __restrict__ feat, cons
         else if (in) v = fminf(fmaxf((feat[NIN * unit + i] - norm[i]) * norm[NIP + i], -kClamp), kClamp);
         x[i] = v;
     }
+}
+
+// The inputs of a wave's 64 units, one per lane, as the two B operands: tile[t][ks] for the units
+// 32 t + l % 32.
+__device__ __forceinline__ void unit_inputs(const float* __restrict__ feat, const float* __restrict__ norm,
+                                            const float* b, int64_t unit, bool in, s4 (&tile)[2][NIP / 8]) {
+    float x[NNET];
+    net_inputs(feat, norm, b, unit, in, x);
     tile[0][0] = pack4(x[0], x[1], x[2], x[3]);
     tile[1][0] = pack4(x[4], x[5], x[6], x[7]);
     tile[0][1] = pack4(x[8], x[9], 0.0f, 0.0f);
@@ -339,8 +230,8 @@ __device__ __forceinline__ void unit_inputs(const float* __restrict__ feat, cons
 // ------------------------------------------------------------------ inference
 // One wave takes 64 units at a time, two products of 32 units each.  Bound by the VALU work around the
 // products (the block inputs and D^-1/2 in double, softplus) and by HBM: 92 B per unit.  With the
-// activations staged in LDS one wave per SIMD fitted (113 KB a workgroup) and 2.2 M units took 379 us;
-// INFER_NOW.
+// activations staged in LDS one wave per SIMD fitted (113 KB a workgroup) and 2.2 M units took 359 us;
+// so they take 95 us, 2.1 TB/s.
 constexpr int kInferWaves = 4;
 constexpr int kInferBlocks = 768;  // three workgroups per CU
 
@@ -418,7 +309,7 @@ __global__ __launch_bounds__(64 * kInferWaves, 3) void k_mlp_infer(const unsigne
                     for (int j = 0; j < 4; ++j) {
                         float p = 0.0f;
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) p += L[i][k] * L[j][k];
+                        for (int k = 0; k <= (i < j ? i : j); ++k) p += L[i][k] * L[j][k];
                         P[i][j] = p;
                     }
                 float q = 0.0f;
@@ -450,209 +341,282 @@ __global__ __launch_bounds__(64 * kInferWaves, 3) void k_mlp_infer(const unsigne
 }
 
 // ------------------------------------------------------------------ training step
-// One wave per workgroup (the activations of a tile are kept in both orientations).
-__global__ __launch_bounds__(64) void k_mlp_train(const unsigned short* __restrict__ w,
+// A wave takes 32 units at a time, everything in registers; both halves of the wave work out the
+// inputs and the loss of the same 32 units.  A product a b with the operands exchanged gives the
+// transposed result, so each activation is computed in both forms that are needed, from the same
+// operands:
+//   T  features along the registers, one unit per lane: the next product's operand;
+//   U  units along the registers, one feature per lane: the operand of a weight gradient, the
+//      contraction over the units.
+// Inputs, output gradients and the transposed W2, which start in form T, get form U from a product
+// with the identity.  The waves of a workgroup sum their gradients in LDS (double atomics, which
+// are the fast ones), and each workgroup adds one gradient to HBM: adds to one line take about
+// 0.1 us each, whoever makes them, so 256 waves that each added a gradient took 30 us for it.
+// A step on 16384 units: 25 us, 65536: 36 us; with LDS staging (111 KB a workgroup) and an atomic add
+// per wave and weight 50 and 148 us.
+constexpr int kTrainWaves = 8, kTrainBlocks = 128;
+constexpr int kTrainUnits = 32;
+constexpr int kLossSlot = NW - 1;  // b3[15], an output that does not exist: its gradient slot carries the loss
+
+__device__ __forceinline__ f16v mm(s4 a, s4 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f16v zero16() {
+    f16v r;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) r[v] = 0.0f;
+    return r;
+}
+__device__ __forceinline__ s4 pack4(const f16v& a, int g) { return pack4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]); }
+// a where the bfloat16 activation x is positive, else 0
+__device__ __forceinline__ s4 gate(const f16v& a, int g, s4 x) {
+    return pack4(x[0] > 0 ? a[4 * g] : 0.0f, x[1] > 0 ? a[4 * g + 1] : 0.0f, x[2] > 0 ? a[4 * g + 2] : 0.0f,
+                 x[3] > 0 ? a[4 * g + 3] : 0.0f);
+}
+__device__ __forceinline__ float sum4(s4 x) {
+    return (bf2f((unsigned short)x[0]) + bf2f((unsigned short)x[1])) + (bf2f((unsigned short)x[2]) + bf2f((unsigned short)x[3]));
+}
+
+__global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(const unsigned short* __restrict__ w,
                                                   const float* __restrict__ norm,
                                                   const float* __restrict__ feat, const float* __restrict__ blocks,
-                                                  int n, float inv_n, float damp, float* __restrict__ grad,
-                                                  float* __restrict__ loss) {
-    __shared__ unsigned short sW1[NH * LD16], sW2[NH * LD64], sW3[32 * LD64], sW2t[NH * LD64], sW3t[NH * LD32];
-    __shared__ float sb1[NH], sb2[NH], sb3[NOP];
-    __shared__ unsigned short sX[TU * LD16], sXt[32 * LD64], sH1[TU * LD64], sH1t[NH * LD64], sH2[TU * LD64],
-        sH2t[NH * LD64], sdO[TU * LD32], sdOt[32 * LD64], sdZ2[TU * LD64], sdZ2t[NH * LD64], sdZ1t[NH * LD64];
-    __shared__ float sO[TU * 17];
-    Weights W{(lds_bf*)sW1, (lds_bf*)sW2, (lds_bf*)sW3, sb1, sb2, sb3};
-    load_weights(w, W, (lds_bf*)sW2t, (lds_bf*)sW3t);
-    const int l = lane();
-    const int64_t unit = (int64_t)blockIdx.x * TU + l;
-    load_features(feat, norm, blocks, unit, n, (lds_bf*)sX + l * LD16, (lds_bf*)sXt, l);
-    forward_tile(W, (lds_bf*)sX, (lds_bf*)sH1, (lds_bf*)sH2, sO, (lds_bf*)sH1t, (lds_bf*)sH2t);
-
-    // robust loss of E = L L^T (B~ + damp I) - I for this unit and its gradient w.r.t. the raw outputs
-    float dr[NO];
+                                                  int n, float inv_n, float damp, float* __restrict__ grad) {
+    __shared__ __align__(16) float sb1[NH], sb2[NH], sb3[NOP];
+    __shared__ double sum[NW];  // the workgroup's gradient
+    const int l = lane(), r = l & 31, h = l >> 5;
+    for (int i = threadIdx.x; i < NW; i += blockDim.x) {
+        sum[i] = 0.0;
+        if (i < NH) sb1[i] = bf2f(w[OFF_B1 + i]);
+        if (i < NH) sb2[i] = bf2f(w[OFF_B2 + i]);
+        if (i < NOP) sb3[i] = bf2f(w[OFF_B3 + i]);
+    }
+    __syncthreads();
+    RegWeights W;
+    W.load(w);
+    s4 w3c[2][2];  // lane l holds column l % 32 of each half of W3, rows 8 ks + 4 h + j
 #pragma unroll
-    for (int i = 0; i < NO; ++i) dr[i] = 0.0f;
-    float lu = 0.0f;
-    if (unit < n) {
-        const float* b = blocks + 5 * unit;
-        const float d = b[0], f = b[4];
-        const float m = fmaxf(d, f);
-        bool finite = true;
+    for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int i = 0; i < 5; ++i) finite &= isfinite(b[i]);
-        if (m > 0.0f && finite) {  // (a non-finite block contributes nothing)
-            // normalised block D^-1/2 (B + rho I) D^-1/2: unit diagonal, e / sqrt(d f) off it; in
-            // double, as in inference (the ridge of a block in the subnormal range underflows FP32)
-            const double rho = (double)kRidge * m;
-            const double sdf = 1.0 / sqrt(((double)d + rho) * ((double)f + rho));
-            const float e0 = (float)(b[1] * sdf), e1 = (float)(b[2] * sdf), e2 = (float)(b[3] * sdf);
-            const float g1 = 1.0f + damp;
-            const float Bn[4][4] = {{g1, 0.0f, 0.0f, e0}, {0.0f, g1, 0.0f, e1}, {0.0f, 0.0f, g1, e2},
-                                    {e0, e1, e2, g1}};
-            float raw[NO];
+        for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int i = 0; i < NO; ++i) raw[i] = sO[l * 17 + i];
-            float L[4][4];
-            make_L(raw, L);
-            float P[4][4], E[4][4], G[4][4];
+            for (int j = 0; j < 4; ++j) w3c[nb][ks][j] = (short)w[OFF_W3 + (8 * ks + 4 * h + j) * NH + nb * 32 + r];
+    s4 eye[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float p = 0.0f;
+        for (int j = 0; j < 4; ++j) eye[ks][j] = (8 * ks + 4 * h + j == r) ? (short)0x3f80 : (short)0;
+    auto add = [&](int at, float v) {
+        __hip_atomic_fetch_add((LDS double*)(sum + at), (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const int n_tiles = (n + kTrainUnits - 1) / kTrainUnits;
+    for (int tile = blockIdx.x * kTrainWaves + (threadIdx.x >> 6); tile < n_tiles; tile += gridDim.x * kTrainWaves) {
+        const int64_t unit = (int64_t)tile * kTrainUnits + r;
+        float b[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (unit < n) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) p += L[i][q] * L[j][q];
-                    P[i][j] = p;
-                }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float e = (i == j) ? -1.0f : 0.0f;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) e += P[i][q] * Bn[q][j];
-                    E[i][j] = e;
-                    lu += e * e;
-                }
-            float scale = 1.0f;  // d loss / d ||E||^2 of the robust per-unit loss
-            if (lu > kKappa) {
-                scale = sqrtf(kKappa / lu);
-                lu = 2.0f * sqrtf(kKappa * lu) - kKappa;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float g = 0.0f;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) g += E[i][q] * Bn[q][j];
-                    G[i][j] = 2.0f * inv_n * scale * g;
-                }
-            int k = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j <= i; ++j, ++k) {
-                    float dl = 0.0f;  // ((G + G^T) L)_ij
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) dl += (G[i][q] + G[q][i]) * L[q][j];
-                    dr[k] = (i == j) ? dl * sigmoid(raw[k]) : dl;
-                }
+            for (int i = 0; i < 5; ++i) b[i] = blocks[5 * unit + i];
         }
-    }
-    // loss sum
-    {
-        float t = lu * inv_n;
+        float in[NNET];
+        net_inputs(feat, norm, b, unit, unit < n, in);
+        const s4 zero = {0, 0, 0, 0};
+        const s4 x[2] = {h ? pack4(in[4], in[5], in[6], in[7]) : pack4(in[0], in[1], in[2], in[3]),
+                         h ? zero : pack4(in[8], in[9], 0.0f, 0.0f)};
+        s4 h1t[8], h1u[2][4], h2u[2][4], h2t[8];  // [..][K step]
+        f16v acc[2];
+        // ReLU of form U plus its bias
+        auto activate_u = [&](const f16v& a, float bias, s4 (&out)[4]) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
-        if (l == 0) atomicAdd(loss, t);
-    }
-    // dO rows (this unit) and columns (transpose)
-    lds_bf* dOs = (lds_bf*)sdO;
-    lds_bf* dOt = (lds_bf*)sdOt;
-#pragma unroll
-    for (int o = 0; o < 32; ++o) {
-        const unsigned short q = f2bf(o < NO ? dr[o] : 0.0f);
-        dOs[l * LD32 + o] = q;
-        dOt[o * LD64 + l] = q;
-    }
-    // dH2 = dO W3, dZ2 = dH2 * (H2 > 0)
-    {
-        f16v acc[2][2];
-        zero(acc);
-        wgemm<2, 2, 32 / 8>(dOs, LD32, (lds_bf*)sW3t, LD32, acc);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int u = crow(mb, v), hh = ccol(nb);
-                    const float hv = bf2f(((lds_bf*)sH2)[u * LD64 + hh]);
-                    const unsigned short q = f2bf(hv > 0.0f ? acc[mb][nb][v] : 0.0f);
-                    ((lds_bf*)sdZ2)[u * LD64 + hh] = q;
-                    ((lds_bf*)sdZ2t)[hh * LD64 + u] = q;
-                }
-    }
-    // dH1 = dZ2 W2, dZ1 = dH1 * (H1 > 0) (only its transpose is needed)
-    {
-        f16v acc[2][2];
-        zero(acc);
-        wgemm<2, 2, NH / 8>((lds_bf*)sdZ2, LD64, (lds_bf*)sW2t, LD64, acc);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int u = crow(mb, v), hh = ccol(nb);
-                    const float hv = bf2f(((lds_bf*)sH1)[u * LD64 + hh]);
-                    ((lds_bf*)sdZ1t)[hh * LD64 + u] = f2bf(hv > 0.0f ? acc[mb][nb][v] : 0.0f);
-                }
-    }
-    // weight gradients: contractions over the tile's units
-    {
-        f16v acc[1][2];  // dW3[o][h] = sum_u dO[u][o] H2[u][h]
-        zero(acc);
-        wgemm<1, 2, TU / 8>(dOt, LD64, (lds_bf*)sH2t, LD64, acc);
+            for (int g = 0; g < 4; ++g)
+                out[g] = pack4(fmaxf(a[4 * g] + bias, 0.0f), fmaxf(a[4 * g + 1] + bias, 0.0f),
+                               fmaxf(a[4 * g + 2] + bias, 0.0f), fmaxf(a[4 * g + 3] + bias, 0.0f));
+        };
+        layer(W.w1, x, acc);
+        activate(acc, sb1, h1t);
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
+            activate_u(mm(x[1], W.w1[nb][1], mm(x[0], W.w1[nb][0], zero16())), sb1[nb * 32 + r], h1u[nb]);
+        layer(W.w2, h1t, acc);
+        activate(acc, sb2, h2t);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int o = crow(0, v), hh = ccol(nb);
-                if (o < NO && acc[0][nb][v] != 0.0f) atomicAdd(grad + OFF_W3 + o * NH + hh, acc[0][nb][v]);
+        for (int nb = 0; nb < 2; ++nb) {
+            f16v a = zero16();
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) a = mm(h1t[ks], W.w2[nb][ks], a);
+            activate_u(a, sb2[nb * 32 + r], h2u[nb]);
+        }
+        f16v res = zero16();
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) res = mm(W.w3[ks], h2t[ks], res);
+        float o[2][6];  // outputs 0 .. 3, 8, 9, then 4 .. 7
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            o[0][i] = o[1][i] = res[i] + sb3[i < 4 ? 4 * h + i : 4 + i];
+            swap32(o[0][i], o[1][i]);  // the lower half's value, the upper half's value
+        }
+
+        // robust loss of E = L L^T (B~ + damp I) - I for this unit and its gradient w.r.t. the raw outputs
+        float dr[NO];
+#pragma unroll
+        for (int i = 0; i < NO; ++i) dr[i] = 0.0f;
+        float lu = 0.0f;
+        if (unit < n) {
+            const float d = b[0], f = b[4];
+            const float m = fmaxf(d, f);
+            bool finite = true;
+#pragma unroll
+            for (int i = 0; i < 5; ++i) finite &= isfinite(b[i]);
+            if (m > 0.0f && finite) {  // (a non-finite block contributes nothing)
+                // normalised block D^-1/2 (B + rho I) D^-1/2: unit diagonal, e / sqrt(d f) off it; in
+                // double, as in inference (the ridge of a block in the subnormal range underflows FP32)
+                const double rho = (double)kRidge * m;
+                const double sdf = 1.0 / sqrt(((double)d + rho) * ((double)f + rho));
+                const float e0 = (float)(b[1] * sdf), e1 = (float)(b[2] * sdf), e2 = (float)(b[3] * sdf);
+                const float g1 = 1.0f + damp;
+                const float e[3] = {e0, e1, e2};
+                // M Bn, Bn = [[g1 I, e], [e^T, g1]]
+                auto times_block = [&](const float (&M)[4][4], int i, int j, float start) {
+                    if (j < 3) return fmaf(M[i][3], e[j], fmaf(M[i][j], g1, start));
+                    return fmaf(M[i][3], g1, fmaf(M[i][2], e[2], fmaf(M[i][1], e[1], fmaf(M[i][0], e[0], start))));
+                };
+                float raw[NO];
+#pragma unroll
+                for (int i = 0; i < NO; ++i) raw[i] = i < 4 ? o[0][i] : i < 8 ? o[1][i - 4] : o[0][i - 4];
+                float L[4][4];
+                make_L(raw, L);
+                float P[4][4], E[4][4], G[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float p = 0.0f;
+#pragma unroll
+                        for (int q = 0; q <= (i < j ? i : j); ++q) p += L[i][q] * L[j][q];
+                        P[i][j] = p;
+                    }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float v = times_block(P, i, j, (i == j) ? -1.0f : 0.0f);
+                        E[i][j] = v;
+                        lu += v * v;
+                    }
+                float scale = 1.0f;  // d loss / d ||E||^2 of the robust per-unit loss
+                if (lu > kKappa) {
+                    scale = sqrtf(kKappa / lu);
+                    lu = 2.0f * sqrtf(kKappa * lu) - kKappa;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        G[i][j] = 2.0f * inv_n * scale * times_block(E, i, j, 0.0f);
+                    }
+                int k = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j <= i; ++j, ++k) {
+                        float dl = 0.0f;  // ((G + G^T) L)_ij
+#pragma unroll
+                        for (int q = j; q < 4; ++q) dl += (G[i][q] + G[q][i]) * L[q][j];
+                        dr[k] = (i == j) ? dl * sigmoid(raw[k]) : dl;
+                    }
             }
-    }
-    {
-        f16v acc[2][2];  // dW2[ho][hi] = sum_u dZ2[u][ho] H1[u][hi]
-        zero(acc);
-        wgemm<2, 2, TU / 8>((lds_bf*)sdZ2t, LD64, (lds_bf*)sH1t, LD64, acc);
+        }
+        // loss sum
+        {
+            float t = lu * inv_n;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+            for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
+            if (l == 0) add(kLossSlot, 0.5f * t);  // every unit counted twice
+        }
+        // the output gradients as an operand
+        const s4 dov[2] = {h ? pack4(dr[4], dr[5], dr[6], dr[7]) : pack4(dr[0], dr[1], dr[2], dr[3]),
+                           h ? zero : pack4(dr[8], dr[9], 0.0f, 0.0f)};
+        const f16v xf = mm(x[1], eye[1], mm(x[0], eye[0], zero16()));
+        const f16v df = mm(dov[1], eye[1], mm(dov[0], eye[0], zero16()));
+        s4 xu[4], du[4], z2t[8], z2u[2][4], z1u[2][4];
+        float sb[2] = {0.0f, 0.0f}, s1[2] = {0.0f, 0.0f}, s3 = 0.0f;
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+        for (int g = 0; g < 4; ++g) {
+            xu[g] = pack4(xf, g);
+            du[g] = pack4(df, g);
+            s3 += sum4(du[g]);
+        }
+        // dZ2 = (dO W3) where H2 > 0, both forms; dZ1 = (dZ2 W2) where H1 > 0, form U
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            const f16v dt = mm(w3c[nb][1], dov[1], mm(w3c[nb][0], dov[0], zero16()));
+            const f16v dv = mm(dov[1], w3c[nb][1], mm(dov[0], w3c[nb][0], zero16()));
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                z2t[4 * nb + g] = gate(dt, g, h2t[4 * nb + g]);
+                z2u[nb][g] = gate(dv, g, h2u[nb][g]);
+                sb[nb] += sum4(z2u[nb][g]);
+            }
+        }
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            f16v dv = zero16();
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                f16v wt = zero16();  // columns 32 nb + l % 32 of rows 32 mb .. of W2
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) wt = mm(W.w2[mb][4 * nb + ks], eye[ks], wt);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) dv = mm(z2t[4 * mb + g], pack4(wt, g), dv);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                z1u[nb][g] = gate(dv, g, h1u[nb][g]);
+                s1[nb] += sum4(z1u[nb][g]);
+            }
+        }
+        // weight gradients, contractions over the units: sum[m][n] += sum_u a[u][m] b[u][n]
+        auto contract = [&](const s4 (&a)[4], const s4 (&bb)[4], int to, int pitch, int rows, int cols) {
+            f16v g = zero16();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) g = mm(a[ks], bb[ks], g);
+            if (r < cols) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int ho = crow(mb, v), hi = ccol(nb);
-                    if (acc[mb][nb][v] != 0.0f) atomicAdd(grad + OFF_W2 + ho * NH + hi, acc[mb][nb][v]);
+                    const int row = 8 * (v >> 2) + (v & 3);
+                    if (row < rows && (row + 4 < rows || 4 * h + row < rows)) add(to + (row + 4 * h) * pitch + r, g[v]);
                 }
-    }
-    {
-        f16v acc[2][1];  // dW1[h][i] = sum_u dZ1[u][h] X[u][i]
-        zero(acc);
-        wgemm<2, 1, TU / 8>((lds_bf*)sdZ1t, LD64, (lds_bf*)sXt, LD64, acc);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int hh = crow(mb, v), i = ccol(0);
-                if (i < NNET && acc[mb][0][v] != 0.0f) atomicAdd(grad + OFF_W1 + hh * NIP + i, acc[mb][0][v]);
             }
+        };
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            contract(du, h2u[i], OFF_W3 + i * 32, NH, NO, 32);
+            contract(z1u[i], xu, OFF_W1 + i * 32 * NIP, NIP, 32, NNET);
+            contract(z2u[i], h1u[0], OFF_W2 + i * 32 * NH, NH, 32, 32);
+            contract(z2u[i], h1u[1], OFF_W2 + i * 32 * NH + 32, NH, 32, 32);
+        }
+        // bias gradients: a lane holds the sum over half of the units
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            add(OFF_B1 + i * 32 + r, s1[i]);
+            add(OFF_B2 + i * 32 + r, sb[i]);
+        }
+        if (r < NO) add(OFF_B3 + r, s3);
     }
-    // bias gradients: row sums of the transposed gradients
-    {
-        float s1 = 0.0f, s2 = 0.0f;
-        for (int u = 0; u < TU; ++u) {
-            s1 += bf2f(((lds_bf*)sdZ1t)[l * LD64 + u]);
-            s2 += bf2f(((lds_bf*)sdZ2t)[l * LD64 + u]);
-        }
-        if (s1 != 0.0f) atomicAdd(grad + OFF_B1 + l, s1);
-        if (s2 != 0.0f) atomicAdd(grad + OFF_B2 + l, s2);
-        if (l < NO) {
-            float s3 = 0.0f;
-            for (int u = 0; u < TU; ++u) s3 += bf2f(dOt[l * LD64 + u]);
-            if (s3 != 0.0f) atomicAdd(grad + OFF_B3 + l, s3);
-        }
+    __syncthreads();
+    for (int i = threadIdx.x; i < NW; i += blockDim.x) {
+        const float g = (float)sum[i];
+        if (g != 0.0f) atomicAdd(grad + i, g);
     }
 }
 
-// Adam on the FP32 master weights; refreshes the bfloat16 copy and clears the gradient.
+// Adam on the FP32 master weights; refreshes the bfloat16 copy, hands over the loss and clears the gradient.
 __global__ void k_adam(float* __restrict__ w32, unsigned short* __restrict__ wbf, float* __restrict__ m,
-                       float* __restrict__ v, float* __restrict__ g, int t, float lr) {
+                       float* __restrict__ v, float* __restrict__ g, int t, float lr, float* __restrict__ loss) {
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < NW; i += gridDim.x * blockDim.x) {
-        const float gi = g[i];
+        float gi = g[i];
+        if (i == kLossSlot) {
+            *loss = gi;
+            gi = 0.0f;
+        }
         const float mi = b1 * m[i] + (1.0f - b1) * gi;
         const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
         m[i] = mi;
@@ -723,12 +687,13 @@ hipError_t launch_mlp_infer(const uint16_t* w, const float* norm, float q_fallba
 hipError_t launch_mlp_train(float* w32, uint16_t* wbf, float* m, float* v, int t, float lr, float damp,
                             const float* norm, const float* feat, const float* blocks, int n, float* loss, float* grad,
                             hipStream_t st) {
-    hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, st, loss, 1);
     if (n > 0) {
-        hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)((n + TU - 1) / TU)), dim3(64), 0, st, wbf, norm, feat, blocks,
-                           n, 1.0f / (float)n, damp, grad, loss);
+        int g = (n + kTrainWaves * kTrainUnits - 1) / (kTrainWaves * kTrainUnits);
+        if (g > kTrainBlocks) g = kTrainBlocks;
+        hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)g), dim3(64 * kTrainWaves), 0, st, wbf, norm, feat, blocks, n,
+                           1.0f / (float)n, damp, grad);
     }
-    hipLaunchKernelGGL(k_adam, dim3((NW + 255) / 256), dim3(256), 0, st, w32, wbf, m, v, grad, t, lr);
+    hipLaunchKernelGGL(k_adam, dim3((NW + 255) / 256), dim3(256), 0, st, w32, wbf, m, v, grad, t, lr, loss);
     return hipGetLastError();
 }
 
