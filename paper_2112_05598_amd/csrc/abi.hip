@@ -1,6 +1,7 @@
 // Host side of the C ABI declared in include/perf_gn.h.
 #include <math.h>
 #include <stdarg.h>
+#include <stddef.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -31,9 +32,7 @@ struct perf_scene {
     float* mlpnorm;
     float q_fallback;
     bool mlp_ready;
-    double host_scalars[S_COUNT];
-    double host_hist[4 * PERF_MAX_PCG];
-    int host_flags[I_COUNT];
+    SolveState host;  // the last solve's scalars, flags and history
 };
 
 namespace {
@@ -146,7 +145,7 @@ Layout make_layout(const perf_scene_desc& d, int n_cams) {
     const int64_t units = (int64_t)d.nx * d.ny * d.nz + (int64_t)d.n_layers * d.env_w * d.env_h;
     const int64_t P = 4 * units;
     const Geo g = make_geo(d, n_cams);
-    L.n_partials = std::max<int64_t>(2 * kVecGrid, std::max(ray_blocks(g, false), ray_blocks(g, true)));
+    L.n_partials = std::max<int64_t>(3 * kVecGrid, std::max(ray_blocks(g, false), ray_blocks(g, true)));
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -155,9 +154,7 @@ Layout make_layout(const perf_scene_desc& d, int n_cams) {
     };
     L.cams = take(sizeof(DevCam) * (size_t)n_cams);
     L.partials = take(sizeof(double) * (size_t)L.n_partials);
-    L.scalars = take(sizeof(double) * S_COUNT);
-    L.hist = take(sizeof(double) * 4 * PERF_MAX_PCG);
-    L.iflags = take(sizeof(int) * I_COUNT);
+    L.state = take(sizeof(SolveState));
     L.vr = take(sizeof(float) * (size_t)P);
     L.vz = take(sizeof(float) * (size_t)P);
     L.vp = take(sizeof(float) * (size_t)P);
@@ -231,9 +228,10 @@ int32_t perf_init_scene(const perf_scene_desc* desc, const perf_camera* cams, in
     s->n_grad_blocks = ray_blocks(s->geo, split_rays(M_GRAD, s->geo));
     s->cams = (DevCam*)(s->ws + L.cams);
     s->partials = (double*)(s->ws + L.partials);
-    s->scalars = (double*)(s->ws + L.scalars);
-    s->hist = (double*)(s->ws + L.hist);
-    s->iflags = (int*)(s->ws + L.iflags);
+    SolveState* state = (SolveState*)(s->ws + L.state);
+    s->scalars = state->scalars;
+    s->iflags = state->iflags;
+    s->hist = state->hist;
     s->vr = (float*)(s->ws + L.vr);
     s->vz = (float*)(s->ws + L.vz);
     s->vp = (float*)(s->ws + L.vp);
@@ -345,8 +343,7 @@ int32_t perf_apply_JtJ(perf_scene* s, const void* d_x, const float* d_v, float* 
 }
 
 static int32_t grad_pass(perf_scene* s, const void* xg, float* grad, float* blocks, bool want_F) {
-    if (grad) CK(launch_zero(grad, s->P, s->stream));
-    if (blocks) CK(launch_zero(blocks, 5 * s->units, s->stream));
+    CK(launch_zero(grad, grad ? s->P : 0, s->stream, blocks, blocks ? 5 * s->units : 0));
     RayArgs a = base_args(s);
     a.x = xg;
     a.targets = s->targets;
@@ -428,15 +425,21 @@ int32_t perf_pack_bf16(const float* d_in, uint16_t* d_out, int64_t n, void* stre
 }
 
 // F(proj(x + gamma delta)) on the device into scalars[S_TMP]; the trial point is left in
-// vxt (FP32) and, for BF16 storage, in xb16.
-static int32_t trial_objective(perf_scene* s, const float* d_x, const float* d_delta, float gamma) {
-    CK(launch_trial(d_x, d_delta, gamma, s->units, s->geo.nvox, s->vxt, s->xb16, s->stream));
+// vxt (FP32) and, for BF16 storage, in xb16.  batch >= 0: trial `batch` of a batch of the line search,
+// into scalars[S_TMP + batch]; skipped once a trial of the batch exceeded the one before it (prev
+// before the first).
+static int32_t trial_objective(perf_scene* s, const float* d_x, const float* d_delta, float gamma, int batch = -1,
+                               double prev = 0.0) {
+    int* done = batch >= 0 ? s->iflags + I_SEARCHED : nullptr;
+    CK(launch_trial(d_x, d_delta, gamma, s->units, s->geo.nvox, s->vxt, s->xb16, s->stream, done, batch == 0));
     RayArgs a = base_args(s);
     a.x = s->xb16 ? (const void*)s->xb16 : (const void*)s->vxt;
     a.targets = s->targets;
     a.partials = s->partials;
+    a.done = batch > 0 ? done : nullptr;
     CK(launch_ray(M_RENDER, s->desc.param_dtype, s->geo, a, s->stream));
-    CK(launch_sum_partials(s->partials, s->n_render_blocks, 0.5, s->scalars + S_TMP, s->stream));
+    if (batch >= 0) CK(launch_sum_trial(s->partials, s->n_render_blocks, batch, prev, s->scalars + S_TMP, done, s->stream));
+    else CK(launch_sum_partials(s->partials, s->n_render_blocks, 0.5, s->scalars + S_TMP, s->stream));
     return PERF_OK;
 }
 
@@ -551,32 +554,20 @@ struct SolveOut {
 static int32_t solve_and_search(perf_scene* s, const void* xg, float* d_x, const perf_pcg_opts* opts,
                                 int apply_kind, hipEvent_t* ev, hipEvent_t* jev, SolveOut* out) {
     hipStream_t st = s->stream;
-    s->host_scalars[S_MAXITERS] = opts->max_iters;
-    s->host_scalars[S_RELTOL] = opts->rel_tol;
-    s->host_scalars[S_ABSEPS] = opts->abs_eps;
-    s->host_scalars[S_STALL] = opts->stall_ratio;
-    CK(hipMemcpyAsync(s->scalars + S_MAXITERS, s->host_scalars + S_MAXITERS, 4 * sizeof(double),
-                      hipMemcpyHostToDevice, st));
-    CK(launch_zero(reinterpret_cast<float*>(s->hist), 8 * PERF_MAX_PCG, st));
-    CK(launch_pcg_init(apply_kind, s->vr, s->minv, s->vr, s->vz, s->vp, s->vdelta, s->units, s->partials, s->scalars,
-                       s->iflags, st));
+    const PcgVectors v{s->minv, s->vr, s->vz, s->vp, s->vAp, s->vdelta};
+    const PcgStop stop{opts->max_iters, opts->rel_tol, opts->abs_eps, opts->stall_ratio};
+    CK(launch_pcg_init(apply_kind, v, s->units, s->partials, s->scalars, s->hist, s->iflags, st));
     const bool poll = opts->rel_tol > 0.0 || opts->abs_eps > 0.0 || opts->stall_ratio > 0.0;
     int n_jtj = 0;
     for (int it = 0; it < opts->max_iters; ++it) {
-        CK(launch_zero(s->vAp, s->P, st, s->iflags + I_DONE));
         RayArgs a = base_args(s);
         a.x = xg;
         a.v = s->vp;
         a.y = s->vAp;
         a.done = s->iflags + I_DONE;
-        CK(hipEventRecord(jev[2 * it], st));
-        CK(launch_ray(M_JTJ, s->desc.param_dtype, s->geo, a, st));
-        CK(hipEventRecord(jev[2 * it + 1], st));
+        CK(launch_ray(M_JTJ, s->desc.param_dtype, s->geo, a, st, jev[2 * it], jev[2 * it + 1]));
         ++n_jtj;
-        CK(launch_pcg_alpha(s->vp, s->vAp, s->units, s->partials, s->scalars, s->hist, s->iflags, st));
-        CK(launch_pcg_update(apply_kind, s->minv, s->vdelta, s->vr, s->vz, s->vp, s->vAp, s->units, s->partials,
-                             s->scalars, s->hist, s->iflags, st));
-        CK(launch_pcg_direction(s->vz, s->vp, s->units, s->scalars, s->iflags, st));
+        CK(launch_pcg_iteration(apply_kind, v, s->units, it, stop, s->partials, s->scalars, s->hist, s->iflags, st));
         if (poll) {
             int done = 0;
             CK(hipMemcpyAsync(&done, s->iflags + I_DONE, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -584,14 +575,14 @@ static int32_t solve_and_search(perf_scene* s, const void* xg, float* d_x, const
             if (done) break;
         }
     }
-    CK(hipMemcpyAsync(s->host_scalars, s->scalars, sizeof(double) * S_COUNT, hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(s->host_hist, s->hist, sizeof(double) * 4 * PERF_MAX_PCG, hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(s->host_flags, s->iflags, sizeof(int) * I_COUNT, hipMemcpyDeviceToHost, st));
     CK(hipEventRecord(ev[0], st));
+    CK(hipMemcpyAsync(&s->host, s->ws + s->lay.state,
+                      offsetof(SolveState, hist) + sizeof(double) * H_COUNT * (size_t)opts->max_iters,
+                      hipMemcpyDeviceToHost, st));
     CK(hipStreamSynchronize(st));
-    const double F0 = s->host_scalars[S_F];
-    int flags = s->host_flags[I_FLAGS];
-    const int iters = s->host_flags[I_ITERS];
+    const double F0 = s->host.scalars[S_F];
+    int flags = s->host.iflags[I_FLAGS];
+    const int iters = s->host.iflags[I_ITERS];
     // line search (Alg. 3) on F(proj(x + gamma Delta)), capped at ls_max trials
     double gamma = 1.0, mu_acc = F0;
     int trials = 0;
@@ -600,30 +591,36 @@ static int32_t solve_and_search(perf_scene* s, const void* xg, float* d_x, const
         const double fac = opts->ls_factor;
         double g = 1.0, mu_prev = INFINITY, best_mu = INFINITY, best_g = 0.0;
         bool decided = false;
-        while (trials < opts->ls_max) {
-            rc = trial_objective(s, d_x, s->vdelta, (float)g);
-            if (rc != PERF_OK) return rc;
-            double mu = 0.0;
-            rc = read_scalar(s, S_TMP, &mu);
-            if (rc != PERF_OK) return rc;
-            ++trials;
-            if (mu < best_mu) {
-                best_mu = mu;
-                best_g = g;
+        // a batch of trials is enqueued at once; the device skips those behind the one that ends the search
+        while (!decided && trials < opts->ls_max) {
+            const int n = std::min(kTrialBatch, opts->ls_max - trials);
+            double gs[kTrialBatch], mus[kTrialBatch];
+            for (int j = 0; j < n; ++j, g *= fac) {
+                gs[j] = g;
+                rc = trial_objective(s, d_x, s->vdelta, (float)g, j, mu_prev);
+                if (rc != PERF_OK) return rc;
             }
-            if (mu > mu_prev) {
-                if (mu_prev < F0) {
-                    gamma = g / fac;
-                    mu_acc = mu_prev;
-                } else {
-                    gamma = 0.0;
-                    mu_acc = F0;
+            CK(hipMemcpyAsync(mus, s->scalars + S_TMP, sizeof(double) * n, hipMemcpyDeviceToHost, st));
+            CK(hipStreamSynchronize(st));
+            for (int j = 0; j < n && !decided; ++j) {
+                const double mu = mus[j];
+                ++trials;
+                if (mu < best_mu) {
+                    best_mu = mu;
+                    best_g = gs[j];
                 }
-                decided = true;
-                break;
+                if (mu > mu_prev) {
+                    if (mu_prev < F0) {
+                        gamma = gs[j] / fac;
+                        mu_acc = mu_prev;
+                    } else {
+                        gamma = 0.0;
+                        mu_acc = F0;
+                    }
+                    decided = true;
+                }
+                mu_prev = mu;
             }
-            g *= fac;
-            mu_prev = mu;
         }
         if (!decided) {
             flags |= PERF_FLAG_LS_CAPPED;
@@ -737,14 +734,15 @@ int32_t perf_gn_step(perf_scene* s, float* d_x, const perf_pcg_opts* opts, perf_
         stats->ls_trials = so.trials;
         stats->flags = flags;
         stats->fallback_iters = fallback_iters;
-        stats->R0 = s->host_scalars[S_R0];
+        stats->R0 = s->host.scalars[S_R0];
         for (int k = 0; k < iters && k < PERF_MAX_PCG; ++k) {
-            stats->alpha[k] = s->host_hist[4 * k + 0];
-            stats->beta[k] = s->host_hist[4 * k + 1];
-            stats->R[k] = s->host_hist[4 * k + 2];
-            stats->pAp[k] = s->host_hist[4 * k + 3];
+            const double* row = s->host.hist + H_COUNT * k;
+            stats->alpha[k] = row[H_ALPHA];
+            stats->beta[k] = row[H_BETA];
+            stats->R[k] = row[H_R];
+            stats->pAp[k] = row[H_PAP];
         }
-        if (iters < PERF_MAX_PCG && (flags & PERF_FLAG_BREAKDOWN)) stats->pAp[iters] = s->host_hist[4 * iters + 3];
+        if (iters < PERF_MAX_PCG && (flags & PERF_FLAG_BREAKDOWN)) stats->pAp[iters] = s->host.hist[H_COUNT * iters + H_PAP];
         float ms = 0.0f;
         for (int i = 0; i < 5; ++i) {
             CK(hipEventElapsedTime(&ms, ev[i], ev[i + 1]));

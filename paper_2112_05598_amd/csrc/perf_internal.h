@@ -41,28 +41,34 @@ struct Geo {
 
 // Device scalars of a Gauss-Newton step (FP64), indices into the scalar array.
 enum Scalar {
-    S_RZ = 0,      // r_k^T z_k
-    S_PAP = 1,     // p_k^T A p_k
-    S_ALPHA = 2,
-    S_BETA = 3,
-    S_R = 4,       // r_{k+1}^T r_{k+1}
-    S_RPREV = 5,
-    S_R0 = 6,
-    S_F = 7,       // objective of the last render / grad pass
-    S_RZNEW = 8,
-    S_MAXITERS = 9,
-    S_RELTOL = 10,
-    S_ABSEPS = 11,
-    S_STALL = 12,
-    S_TMP = 16,    // scratch for perf_objective etc.
+    S_R0 = 0,      // r_0^T r_0
+    S_F = 1,       // objective of the gradient pass
+    S_TMP = 16,    // objectives of trial points: one (perf_objective) or a batch of kTrialBatch
     S_COUNT = 32
 };
+constexpr int kTrialBatch = 4;  // line-search trials enqueued between two readbacks
+// One row of the solve's history per iteration (FP64).
+enum Hist {
+    H_ALPHA = 0,
+    H_BETA = 1,
+    H_R = 2,      // r_{k+1}^T r_{k+1}
+    H_PAP = 3,    // p_k^T A p_k
+    H_RZ = 4,     // r_k^T z_k
+    H_COUNT = 6
+};
+constexpr int kHistDoubles = H_COUNT * (PERF_MAX_PCG + 1);
 // Device int flags.
-enum IFlag { I_DONE = 0, I_ITERS = 1, I_FLAGS = 2, I_NONFINITE = 3, I_COUNT = 16 };
+enum IFlag { I_DONE = 0, I_ITERS = 1, I_FLAGS = 2, I_NONFINITE = 3, I_SEARCHED = 4, I_COUNT = 64 };
+// Scalars, flags and history are one block of the workspace, copied to the host in one piece.
+struct SolveState {
+    double scalars[S_COUNT];
+    int iflags[I_COUNT];
+    double hist[kHistDoubles];
+};
 
 // Workspace layout (offsets in bytes from the workspace base).
 struct Layout {
-    size_t cams, partials, scalars, hist, iflags;
+    size_t cams, partials, state;
     size_t vr, vz, vp, vAp, vdelta, vxt, blocks, minv, xb16, feat, mlpw, mlpnorm;
     size_t total;
     int64_t n_partials;
@@ -94,26 +100,34 @@ struct RayArgs {
 // four lanes per ray (split_rays: the rule launch_ray goes by)
 int64_t ray_blocks(const Geo& g, bool split);
 bool split_rays(int mode, const Geo& g);
-hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st);
+// begin, end (both or neither): events that take the kernel's own start and end
+hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st,
+                      hipEvent_t begin = nullptr, hipEvent_t end = nullptr);
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,
                             hipStream_t st);
 
 // ---------------------------------------------------------------- launchers (vector.hip)
-hipError_t launch_zero(float* p, int64_t n, hipStream_t st, const int* done = nullptr);
+// zeroes p[0 .. n) and q[0 .. m)
+hipError_t launch_zero(float* p, int64_t n, hipStream_t st, float* q = nullptr, int64_t m = 0);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);
 hipError_t launch_sum_partials(const double* partials, int64_t n, double scale, double* out, hipStream_t st);
 hipError_t launch_precond_invert(int kind, const float* blocks, int64_t units, float* out, hipStream_t st);
-hipError_t launch_pcg_init(int kind, const float* b, const float* minv, float* r, float* z, float* p, float* delta,
-                           int64_t units, double* partials, double* scalars, int* iflags, hipStream_t st);
-hipError_t launch_pcg_alpha(const float* p, const float* Ap, int64_t units, double* partials, double* scalars,
-                            double* hist, int* iflags, hipStream_t st);
-hipError_t launch_pcg_update(int kind, const float* minv, float* delta, float* r, float* z, const float* p,
-                             const float* Ap, int64_t units, double* partials, double* scalars, double* hist,
-                             int* iflags, hipStream_t st);
-hipError_t launch_pcg_direction(const float* z, float* p, int64_t units, const double* scalars, const int* iflags,
-                                hipStream_t st);
+hipError_t launch_sum_trial(const double* partials, int64_t n, int j, double prev, double* mu, int* done, hipStream_t st);
+struct PcgVectors {
+    const float* minv;
+    float *r, *z, *p, *Ap, *delta;
+};
+struct PcgStop {
+    int max_iters;
+    double rel_tol, abs_eps, stall;
+};
+// r holds b on entry; leaves Ap = 0
+hipError_t launch_pcg_init(int kind, const PcgVectors& v, int64_t units, double* partials, double* scalars, double* hist,
+                           int* iflags, hipStream_t st);
+hipError_t launch_pcg_iteration(int kind, const PcgVectors& v, int64_t units, int it, const PcgStop& stop,
+                                double* partials, const double* scalars, double* hist, int* iflags, hipStream_t st);
 hipError_t launch_trial(const float* x, const float* delta, float gamma, int64_t units, int nvox, float* xt,
-                        uint16_t* xb16, hipStream_t st);
+                        uint16_t* xb16, hipStream_t st, int* done = nullptr, bool first = false);
 hipError_t launch_pack_bf16(const float* in, uint16_t* out, int64_t n, hipStream_t st);
 hipError_t launch_check_finite(const float* p, int64_t n, int* flag, hipStream_t st);
 hipError_t launch_unit_features(const void* x, int x_dtype, const float* blocks, int64_t units, float* feat,

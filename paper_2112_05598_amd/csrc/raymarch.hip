@@ -30,6 +30,8 @@
 // corners are always distinct voxels, which the per-ray window of the gradient pass needs.
 #include "perf_internal.h"
 
+#include <hip/hip_ext.h>
+
 #include <math.h>
 
 namespace perf {
@@ -1907,23 +1909,25 @@ __global__ __launch_bounds__(kBlock) void k_footprint(Geo G, const DevCam* cams,
 }
 
 template <int MODE, int PD, int KIND>
-hipError_t launch_one(const Geo& g, const RayArgs& a, hipStream_t st) {
+hipError_t launch_one(const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin, hipEvent_t end) {
     const unsigned grid = (unsigned)ray_blocks(g, KIND != S_ONE);
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), dim3(kBlock), 0, st, g, a);
+    // events taken from the dispatch itself: recorded around it they cost 5 us each on the stream
+    if (begin) hipExtLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), dim3(kBlock), 0, st, begin, end, 0, g, a);
+    else hipLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), dim3(kBlock), 0, st, g, a);
     return hipGetLastError();
 }
 
 template <int PD, int KIND>
-hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st) {
+hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin, hipEvent_t end) {
     switch (mode) {
-        case M_RENDER: return launch_one<M_RENDER, PD, KIND>(g, a, st);
-        case M_JVP: return launch_one<M_JVP, PD, KIND>(g, a, st);
-        case M_VJP: return launch_one<M_VJP, PD, KIND>(g, a, st);
-        case M_JTJ: return launch_one<M_JTJ, PD, KIND>(g, a, st);
+        case M_RENDER: return launch_one<M_RENDER, PD, KIND>(g, a, st, begin, end);
+        case M_JVP: return launch_one<M_JVP, PD, KIND>(g, a, st, begin, end);
+        case M_VJP: return launch_one<M_VJP, PD, KIND>(g, a, st, begin, end);
+        case M_JTJ: return launch_one<M_JTJ, PD, KIND>(g, a, st, begin, end);
         case M_GRAD:
-            if (KIND == S_FOUR && !split_rays(M_RENDER, g)) return launch_one<M_GRAD, PD, S_BACK>(g, a, st);
-            return launch_one<M_GRAD, PD, KIND>(g, a, st);
+            if (KIND == S_FOUR && !split_rays(M_RENDER, g)) return launch_one<M_GRAD, PD, S_BACK>(g, a, st, begin, end);
+            return launch_one<M_GRAD, PD, KIND>(g, a, st, begin, end);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1949,11 +1953,14 @@ bool split_rays(int mode, const Geo& g) {
     return ray_blocks(g, false) < few || (scatter && g.pitch > 0.6f);
 }
 
-hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st) {
+hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin,
+                      hipEvent_t end) {
     const bool split = split_rays(mode, g);
     if (param_dtype == PERF_BF16)
-        return split ? launch_mode<PERF_BF16, S_FOUR>(mode, g, a, st) : launch_mode<PERF_BF16, S_ONE>(mode, g, a, st);
-    return split ? launch_mode<PERF_F32, S_FOUR>(mode, g, a, st) : launch_mode<PERF_F32, S_ONE>(mode, g, a, st);
+        return split ? launch_mode<PERF_BF16, S_FOUR>(mode, g, a, st, begin, end)
+                     : launch_mode<PERF_BF16, S_ONE>(mode, g, a, st, begin, end);
+    return split ? launch_mode<PERF_F32, S_FOUR>(mode, g, a, st, begin, end)
+                 : launch_mode<PERF_F32, S_ONE>(mode, g, a, st, begin, end);
 }
 
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,

@@ -2,10 +2,14 @@
 // the line search (Alg. 3).  One thread handles one unit (float4 = the 4 parameters of a
 // voxel or texel) in a grid-stride loop over a fixed grid of kVecGrid workgroups, so every
 // dot product is reduced the same way on every call: FP64 per-thread sums, FP64 wave and
-// workgroup reduction, one partial per workgroup, then a single workgroup adds the
-// partials in index order.  All PCG scalars (alpha, beta, R, r^T z) stay on the device;
-// the stop rules of Alg. 2 are evaluated there and raise a flag that every later kernel
-// of the solve checks, so the host can enqueue a whole solve without reading anything back.
+// workgroup reduction, one partial per workgroup.  The kernel that needs the sum adds the partials
+// itself, every workgroup in the same order: at most 16 KB from L2 each, where a launch of its own
+// takes 4.6 us.  A PCG iteration is then J^T J v and three vector kernels (k_dot, k_pcg_update,
+// k_pcg_direction); with the sums and the clearing of A p in launches of their own it was six, 29 us
+// at 32^3 where J^T J v takes 165.  All PCG scalars stay on the device, one row of `hist` per
+// iteration, so that no workgroup overwrites what another still reads; the stop rules of Alg. 2
+// are evaluated there and raise a flag that every later kernel of the solve checks, so the
+// host can enqueue a whole solve without reading anything back.
 #include "perf_internal.h"
 
 #include <math.h>
@@ -42,19 +46,24 @@ __device__ __forceinline__ void block_sum2(double a, double b, double* oa, doubl
     }
 }
 
-// Sum n partials in a fixed order with one workgroup (deterministic).
+// Sum of n partials by one workgroup of BLOCK threads in a fixed order (deterministic).
+template <int BLOCK>
 __device__ __forceinline__ double fixed_order_sum(const double* p, int64_t n) {
-    __shared__ double red[kVecBlock / 64];
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += kVecBlock) s += p[i];
-    s = wave_sum(s);
+    __shared__ double red[BLOCK / 64];
+    double s[4] = {0.0, 0.0, 0.0, 0.0};  // four loads in flight
+    for (int64_t i = threadIdx.x; i < n; i += 4 * BLOCK) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i + k * BLOCK < n) s[k] += p[i + k * BLOCK];
+    }
+    const double w = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) red[wave] = s;
+    __syncthreads();
+    if (lane == 0) red[wave] = w;
     __syncthreads();
     double t = 0.0;
 #pragma unroll
-    for (int i = 0; i < kVecBlock / 64; ++i) t += red[i];
-    __syncthreads();
+    for (int i = 0; i < BLOCK / 64; ++i) t += red[i];
     return t;
 }
 
@@ -113,10 +122,10 @@ __device__ __forceinline__ float4 precond_apply(const float* __restrict__ minv, 
     }
 }
 
-__global__ void k_zero(float* __restrict__ p, int64_t n, const int* done) {
-    if (done && *done) return;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0f;
+__global__ void k_zero(float* __restrict__ p, int64_t n, float* __restrict__ q, int64_t m) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0.0f;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += stride) q[i] = 0.0f;
 }
 
 __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
@@ -124,9 +133,23 @@ __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
         p[i] = 0ull;
 }
 
-__global__ void k_sum_partials(const double* p, int64_t n, double scale, double* out) {
-    const double s = fixed_order_sum(p, n);
+// One partial per ray workgroup: 125 000 for 16 M rays took a workgroup of 256 threads 150 us.
+constexpr int kSumBlock = 1024;
+__global__ __launch_bounds__(kSumBlock) void k_sum_partials(const double* p, int64_t n, double scale, double* out) {
+    const double s = fixed_order_sum<kSumBlock>(p, n);
     if (threadIdx.x == 0) *out = scale * s;
+}
+
+// The objective of line-search trial j of a batch into mu[j]; raises *done when it exceeds the trial
+// before (prev for the first of the batch), which ends the search (Alg. 3).
+__global__ __launch_bounds__(kSumBlock) void k_sum_trial(const double* p, int64_t n, int j, double prev, double* mu,
+                                                         int* done) {
+    if (j > 0 && *done) return;
+    const double s = 0.5 * fixed_order_sum<kSumBlock>(p, n);
+    if (threadIdx.x == 0) {
+        mu[j] = s;
+        if (s > (j > 0 ? mu[j - 1] : prev)) *done = 1;
+    }
 }
 
 // Scaled form of the preconditioner (Sec. III-G) from the blocks [[d I, e], [e^T, f]], FP64 inside.
@@ -159,11 +182,11 @@ __global__ void k_invert(int kind, const float* __restrict__ blocks, int64_t uni
     }
 }
 
-// r = b, z = M^-1 r, p = z, delta = 0; partials of r.r and r.z
+// r = b, z = M^-1 r, p = z, delta = 0, Ap = 0; partials of r.r and r.z
 template <int KIND>
 __global__ void k_pcg_init(const float4* __restrict__ b, const float* __restrict__ minv, float4* __restrict__ r,
-                           float4* __restrict__ z, float4* __restrict__ p, float4* __restrict__ delta, int64_t units,
-                           double* partials) {
+                           float4* __restrict__ z, float4* __restrict__ p, float4* __restrict__ delta,
+                           float4* __restrict__ Ap, int64_t units, double* partials) {
     double rr = 0.0, rz = 0.0;
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < units; u += (int64_t)gridDim.x * blockDim.x) {
         const float4 ru = b[u];
@@ -172,29 +195,24 @@ __global__ void k_pcg_init(const float4* __restrict__ b, const float* __restrict
         z[u] = zu;
         p[u] = zu;
         delta[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        Ap[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         rr += dot4(ru, ru);
         rz += dot4(ru, zu);
     }
     block_sum2(rr, rz, partials + blockIdx.x, partials + gridDim.x + blockIdx.x);
 }
 
-__global__ void k_pcg_init_fin(const double* partials, int64_t nb, double* sc, int* fl) {
-    const double rr = fixed_order_sum(partials, nb);
-    const double rz = fixed_order_sum(partials + nb, nb);
+__global__ void k_pcg_init_fin(const double* partials, int64_t nb, double* sc, double* hist, int* fl) {
+    const double rr = fixed_order_sum<kVecBlock>(partials, nb);
+    const double rz = fixed_order_sum<kVecBlock>(partials + nb, nb);
+    for (int i = threadIdx.x; i < kHistDoubles; i += kVecBlock)
+        if (i != H_RZ) hist[i] = 0.0;
     if (threadIdx.x == 0) {
         sc[S_R0] = rr;
-        sc[S_RPREV] = rr;
-        sc[S_R] = rr;
-        sc[S_RZ] = rz;
+        hist[H_RZ] = rz;
         fl[I_ITERS] = 0;
-        fl[I_FLAGS] = 0;
-        const int max_iters = (int)sc[S_MAXITERS];
-        if (rr == 0.0 || max_iters <= 0) {
-            fl[I_DONE] = 1;
-            if (rr == 0.0) fl[I_FLAGS] |= PERF_FLAG_CONVERGED;
-        } else {
-            fl[I_DONE] = 0;
-        }
+        fl[I_DONE] = rr == 0.0 ? 1 : 0;
+        fl[I_FLAGS] = rr == 0.0 ? PERF_FLAG_CONVERGED : 0;
     }
 }
 
@@ -207,32 +225,40 @@ __global__ void k_dot(const float4* __restrict__ a, const float4* __restrict__ b
     block_sum2(s, 0.0, partials + blockIdx.x, nullptr);
 }
 
-__global__ void k_pcg_alpha_fin(const double* partials, int64_t nb, double* sc, double* hist, int* fl) {
-    if (fl[I_DONE]) return;
-    const double pAp = fixed_order_sum(partials, nb);
-    if (threadIdx.x == 0) {
-        const int it = fl[I_ITERS];
-        sc[S_PAP] = pAp;
-        hist[4 * it + 3] = pAp;
-        if (!(pAp > 0.0) || !isfinite(pAp)) {
-            fl[I_DONE] = 1;
-            fl[I_FLAGS] |= PERF_FLAG_BREAKDOWN;
-            sc[S_ALPHA] = 0.0;
-        } else {
-            const double a = sc[S_RZ] / pAp;
-            sc[S_ALPHA] = a;
-            hist[4 * it + 0] = a;
-        }
-    }
+// Whether the solve had ended, the same for the whole workgroup: workgroup 0 may raise the flag meanwhile.
+__device__ __forceinline__ bool solve_done(const int* fl) {
+    __shared__ int done;
+    if (threadIdx.x == 0) done = fl[I_DONE];
+    __syncthreads();
+    return done != 0;
 }
 
-// delta += alpha p; r -= alpha Ap; z = M^-1 r; partials of r.r and r.z
+// An iteration is the product and three launches: p.Ap, the update, the direction.  On a level that fits
+// the caches the vectors cost nothing and the launches 5 us each, so every workgroup sums the partials of
+// the launch before it by itself (2 KB of L2 reads, the same order everywhere) instead of waiting for a
+// launch of one workgroup, and the update clears Ap for the next product: 3 launches where 7 were.  With
+// the product's events taken from its dispatch and one readback, a step of 3 iterations on 32^3 voxels
+// went from 1143 to 1058 us, on 64^3 from 5133 to 4873 us.
+// alpha from the partials of p.Ap; delta += alpha p; r -= alpha Ap; z = M^-1 r; Ap = 0 for the next
+// product; partials of r.r and r.z
 template <int KIND>
 __global__ void k_pcg_update(const float* __restrict__ minv, float4* __restrict__ delta, float4* __restrict__ r,
-                             float4* __restrict__ z, const float4* __restrict__ p, const float4* __restrict__ Ap,
-                             int64_t units, double* partials, const double* sc, const int* fl) {
-    if (fl[I_DONE]) return;
-    const float a = (float)sc[S_ALPHA];
+                             float4* __restrict__ z, const float4* __restrict__ p, float4* __restrict__ Ap,
+                             int64_t units, const double* dots, double* partials, double* hist, int* fl) {
+    if (solve_done(fl)) return;
+    const double pAp = fixed_order_sum<kVecBlock>(dots, gridDim.x);
+    const bool broken = !(pAp > 0.0) || !isfinite(pAp);
+    const double alpha = broken ? 0.0 : hist[H_RZ] / pAp;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        hist[H_PAP] = pAp;
+        hist[H_ALPHA] = alpha;
+        if (broken) {
+            fl[I_FLAGS] |= PERF_FLAG_BREAKDOWN;
+            fl[I_DONE] = 1;  // (a workgroup that sees it early would have stopped here too)
+        }
+    }
+    if (broken) return;
+    const float a = (float)alpha;
     double rr = 0.0, rz = 0.0;
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < units; u += (int64_t)gridDim.x * blockDim.x) {
         const float4 pu = p[u], Apu = Ap[u];
@@ -243,58 +269,54 @@ __global__ void k_pcg_update(const float* __restrict__ minv, float4* __restrict_
         delta[u] = d;
         r[u] = ru;
         z[u] = zu;
+        Ap[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         rr += dot4(ru, ru);
         rz += dot4(ru, zu);
     }
     block_sum2(rr, rz, partials + blockIdx.x, partials + gridDim.x + blockIdx.x);
 }
 
-__global__ void k_pcg_update_fin(const double* partials, int64_t nb, double* sc, double* hist, int* fl) {
-    if (fl[I_DONE]) return;
-    const double R = fixed_order_sum(partials, nb);
-    const double rz_new = fixed_order_sum(partials + nb, nb);
-    if (threadIdx.x == 0) {
-        const int it = fl[I_ITERS];
-        hist[4 * it + 2] = R;
-        sc[S_R] = R;
-        const int k = it + 1;
-        fl[I_ITERS] = k;
-        int stop = 0;
-        if (sc[S_ABSEPS] > 0.0 && R < sc[S_ABSEPS]) {
-            stop = 1;
-            fl[I_FLAGS] |= PERF_FLAG_CONVERGED;
-        } else if (sc[S_RELTOL] > 0.0 && sqrt(R / sc[S_R0]) <= sc[S_RELTOL]) {
-            stop = 1;
-            fl[I_FLAGS] |= PERF_FLAG_CONVERGED;
-        } else if (sc[S_STALL] > 0.0 && R / sc[S_RPREV] > sc[S_STALL]) {
-            stop = 1;
-            fl[I_FLAGS] |= PERF_FLAG_STALL;
-        } else if (k >= (int)sc[S_MAXITERS]) {
-            stop = 1;
-        }
-        if (stop) {
-            fl[I_DONE] = 1;
+// R and beta of iteration `it` from the partials, the stop rules (Alg. 2), then p = z + beta p
+__global__ void k_pcg_direction(const float4* __restrict__ z, float4* __restrict__ p, int64_t units,
+                                const double* partials, int it, PcgStop stop, const double* sc, double* hist, int* fl) {
+    if (solve_done(fl)) return;
+    const double R = fixed_order_sum<kVecBlock>(partials, gridDim.x);
+    const double rz_new = fixed_order_sum<kVecBlock>(partials + gridDim.x, gridDim.x);
+    const double R_prev = it > 0 ? hist[H_R - H_COUNT] : sc[S_R0];
+    const double beta = rz_new / hist[H_RZ];
+    int done = 0, flag = 0;
+    if (stop.abs_eps > 0.0 && R < stop.abs_eps) {
+        done = 1;
+        flag = PERF_FLAG_CONVERGED;
+    } else if (stop.rel_tol > 0.0 && sqrt(R / sc[S_R0]) <= stop.rel_tol) {
+        done = 1;
+        flag = PERF_FLAG_CONVERGED;
+    } else if (stop.stall > 0.0 && R / R_prev > stop.stall) {
+        done = 1;
+        flag = PERF_FLAG_STALL;
+    } else if (it + 1 >= stop.max_iters) {
+        done = 1;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        hist[H_R] = R;
+        fl[I_ITERS] = it + 1;
+        if (done) {
+            fl[I_FLAGS] |= flag;
+            fl[I_DONE] = 1;  // (a workgroup that sees it early would have stopped here too)
         } else {
-            sc[S_RPREV] = R;
-            const double beta = rz_new / sc[S_RZ];
-            sc[S_BETA] = beta;
-            sc[S_RZ] = rz_new;
-            hist[4 * it + 1] = beta;
+            hist[H_BETA] = beta;
+            hist[H_COUNT + H_RZ] = rz_new;
         }
     }
-}
-
-__global__ void k_pcg_direction(const float4* __restrict__ z, float4* __restrict__ p, int64_t units, const double* sc,
-                                const int* fl) {
-    if (fl[I_DONE]) return;
-    const float beta = (float)sc[S_BETA];
+    if (done) return;
+    const float b = (float)beta;
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < units; u += (int64_t)gridDim.x * blockDim.x) {
         const float4 zu = z[u];
         float4 pu = p[u];
-        pu.x = zu.x + beta * pu.x;
-        pu.y = zu.y + beta * pu.y;
-        pu.z = zu.z + beta * pu.z;
-        pu.w = zu.w + beta * pu.w;
+        pu.x = zu.x + b * pu.x;
+        pu.y = zu.y + b * pu.y;
+        pu.z = zu.z + b * pu.z;
+        pu.w = zu.w + b * pu.w;
         p[u] = pu;
     }
 }
@@ -307,8 +329,11 @@ __device__ __forceinline__ unsigned short f32_to_bf16_rne(float f) {
 }
 
 // xt = proj(x + gamma delta): sigma >= 0 on voxels, alpha in [0,1] on texels
+// done: a line search that has ended skips the trial; with `first` the search (batch) starts here.
 __global__ void k_trial(const float4* __restrict__ x, const float4* __restrict__ delta, float gamma, int64_t units,
-                        int nvox, float4* __restrict__ xt, ushort4* __restrict__ xb) {
+                        int nvox, float4* __restrict__ xt, ushort4* __restrict__ xb, int* done, bool first) {
+    if (done && first && blockIdx.x == 0 && threadIdx.x == 0) *done = 0;
+    if (done && !first && *done) return;
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < units; u += (int64_t)gridDim.x * blockDim.x) {
         float4 v = x[u];
         if (delta) {
@@ -471,9 +496,9 @@ unsigned grid_for(int64_t n) {
 
 }  // namespace
 
-hipError_t launch_zero(float* p, int64_t n, hipStream_t st, const int* done) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero, dim3(grid_for(n)), dim3(kVecBlock), 0, st, p, n, done);
+hipError_t launch_zero(float* p, int64_t n, hipStream_t st, float* q, int64_t m) {
+    if (n <= 0 && m <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_zero, dim3(grid_for(n > m ? n : m)), dim3(kVecBlock), 0, st, p, n, q, m);
     return hipGetLastError();
 }
 
@@ -484,7 +509,12 @@ hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st) {
 }
 
 hipError_t launch_sum_partials(const double* partials, int64_t n, double scale, double* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kVecBlock), 0, st, partials, n, scale, out);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kSumBlock), 0, st, partials, n, scale, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_trial(const double* partials, int64_t n, int j, double prev, double* mu, int* done, hipStream_t st) {
+    hipLaunchKernelGGL(k_sum_trial, dim3(1), dim3(kSumBlock), 0, st, partials, n, j, prev, mu, done);
     return hipGetLastError();
 }
 
@@ -493,88 +523,61 @@ hipError_t launch_precond_invert(int kind, const float* blocks, int64_t units, f
     return hipGetLastError();
 }
 
-hipError_t launch_pcg_init(int kind, const float* b, const float* minv, float* r, float* z, float* p, float* delta,
-                           int64_t units, double* partials, double* scalars, int* iflags, hipStream_t st) {
+namespace {
+
+template <int KIND>
+void pcg_init_kind(const PcgVectors& v, int64_t units, double* partials, unsigned g, hipStream_t st) {
+    hipLaunchKernelGGL(k_pcg_init<KIND>, dim3(g), dim3(kVecBlock), 0, st, (const float4*)v.r, v.minv, (float4*)v.r,
+                       (float4*)v.z, (float4*)v.p, (float4*)v.delta, (float4*)v.Ap, units, partials);
+}
+
+template <int KIND>
+void pcg_update_kind(const PcgVectors& v, int64_t units, double* partials, double* hist, int* iflags, unsigned g,
+                     hipStream_t st) {
+    hipLaunchKernelGGL(k_pcg_update<KIND>, dim3(g), dim3(kVecBlock), 0, st, v.minv, (float4*)v.delta, (float4*)v.r,
+                       (float4*)v.z, (const float4*)v.p, (float4*)v.Ap, units, partials + 2 * kVecGrid, partials, hist,
+                       iflags);
+}
+
+}  // namespace
+
+hipError_t launch_pcg_init(int kind, const PcgVectors& v, int64_t units, double* partials, double* scalars, double* hist,
+                           int* iflags, hipStream_t st) {
     const unsigned g = grid_for(units);
-    auto B = reinterpret_cast<const float4*>(b);
-    auto R = reinterpret_cast<float4*>(r);
-    auto Z = reinterpret_cast<float4*>(z);
-    auto Pp = reinterpret_cast<float4*>(p);
-    auto D = reinterpret_cast<float4*>(delta);
     switch (kind) {
-        case PERF_PRECOND_NONE:
-            hipLaunchKernelGGL(k_pcg_init<PERF_PRECOND_NONE>, dim3(g), dim3(kVecBlock), 0, st, B, minv, R, Z, Pp, D,
-                               units, partials);
-            break;
-        case PERF_PRECOND_JACOBI:
-            hipLaunchKernelGGL(k_pcg_init<PERF_PRECOND_JACOBI>, dim3(g), dim3(kVecBlock), 0, st, B, minv, R, Z, Pp, D,
-                               units, partials);
-            break;
-        case PERF_PRECOND_BLOCK4:
-            hipLaunchKernelGGL(k_pcg_init<PERF_PRECOND_BLOCK4>, dim3(g), dim3(kVecBlock), 0, st, B, minv, R, Z, Pp, D,
-                               units, partials);
-            break;
-        default:
-            hipLaunchKernelGGL(k_pcg_init<PERF_PRECOND_LEARNED>, dim3(g), dim3(kVecBlock), 0, st, B, minv, R, Z, Pp,
-                               D, units, partials);
-            break;
+        case PERF_PRECOND_NONE: pcg_init_kind<PERF_PRECOND_NONE>(v, units, partials, g, st); break;
+        case PERF_PRECOND_JACOBI: pcg_init_kind<PERF_PRECOND_JACOBI>(v, units, partials, g, st); break;
+        case PERF_PRECOND_BLOCK4: pcg_init_kind<PERF_PRECOND_BLOCK4>(v, units, partials, g, st); break;
+        default: pcg_init_kind<PERF_PRECOND_LEARNED>(v, units, partials, g, st); break;
     }
-    hipLaunchKernelGGL(k_pcg_init_fin, dim3(1), dim3(kVecBlock), 0, st, partials, (int64_t)g, scalars, iflags);
+    hipLaunchKernelGGL(k_pcg_init_fin, dim3(1), dim3(kVecBlock), 0, st, partials, (int64_t)g, scalars, hist, iflags);
     return hipGetLastError();
 }
 
-hipError_t launch_pcg_alpha(const float* p, const float* Ap, int64_t units, double* partials, double* scalars,
-                            double* hist, int* iflags, hipStream_t st) {
+// The vector part of iteration `it`, after Ap = A p: partials[0 .. 2g) hold r.r and r.z, those of p.Ap
+// start at 2 kVecGrid.
+hipError_t launch_pcg_iteration(int kind, const PcgVectors& v, int64_t units, int it, const PcgStop& stop,
+                                double* partials, const double* scalars, double* hist, int* iflags, hipStream_t st) {
     const unsigned g = grid_for(units);
-    hipLaunchKernelGGL(k_dot, dim3(g), dim3(kVecBlock), 0, st, reinterpret_cast<const float4*>(p),
-                       reinterpret_cast<const float4*>(Ap), units, partials, iflags + I_DONE);
-    hipLaunchKernelGGL(k_pcg_alpha_fin, dim3(1), dim3(kVecBlock), 0, st, partials, (int64_t)g, scalars, hist, iflags);
-    return hipGetLastError();
-}
-
-hipError_t launch_pcg_update(int kind, const float* minv, float* delta, float* r, float* z, const float* p,
-                             const float* Ap, int64_t units, double* partials, double* scalars, double* hist,
-                             int* iflags, hipStream_t st) {
-    const unsigned g = grid_for(units);
-    auto D = reinterpret_cast<float4*>(delta);
-    auto R = reinterpret_cast<float4*>(r);
-    auto Z = reinterpret_cast<float4*>(z);
-    auto Pp = reinterpret_cast<const float4*>(p);
-    auto A = reinterpret_cast<const float4*>(Ap);
+    double* row = hist + H_COUNT * it;
+    hipLaunchKernelGGL(k_dot, dim3(g), dim3(kVecBlock), 0, st, (const float4*)v.p, (const float4*)v.Ap, units,
+                       partials + 2 * kVecGrid, iflags + I_DONE);
     switch (kind) {
-        case PERF_PRECOND_NONE:
-            hipLaunchKernelGGL(k_pcg_update<PERF_PRECOND_NONE>, dim3(g), dim3(kVecBlock), 0, st, minv, D, R, Z, Pp, A,
-                               units, partials, scalars, iflags);
-            break;
-        case PERF_PRECOND_JACOBI:
-            hipLaunchKernelGGL(k_pcg_update<PERF_PRECOND_JACOBI>, dim3(g), dim3(kVecBlock), 0, st, minv, D, R, Z, Pp,
-                               A, units, partials, scalars, iflags);
-            break;
-        case PERF_PRECOND_BLOCK4:
-            hipLaunchKernelGGL(k_pcg_update<PERF_PRECOND_BLOCK4>, dim3(g), dim3(kVecBlock), 0, st, minv, D, R, Z, Pp,
-                               A, units, partials, scalars, iflags);
-            break;
-        default:
-            hipLaunchKernelGGL(k_pcg_update<PERF_PRECOND_LEARNED>, dim3(g), dim3(kVecBlock), 0, st, minv, D, R, Z, Pp,
-                               A, units, partials, scalars, iflags);
-            break;
+        case PERF_PRECOND_NONE: pcg_update_kind<PERF_PRECOND_NONE>(v, units, partials, row, iflags, g, st); break;
+        case PERF_PRECOND_JACOBI: pcg_update_kind<PERF_PRECOND_JACOBI>(v, units, partials, row, iflags, g, st); break;
+        case PERF_PRECOND_BLOCK4: pcg_update_kind<PERF_PRECOND_BLOCK4>(v, units, partials, row, iflags, g, st); break;
+        default: pcg_update_kind<PERF_PRECOND_LEARNED>(v, units, partials, row, iflags, g, st); break;
     }
-    hipLaunchKernelGGL(k_pcg_update_fin, dim3(1), dim3(kVecBlock), 0, st, partials, (int64_t)g, scalars, hist, iflags);
-    return hipGetLastError();
-}
-
-hipError_t launch_pcg_direction(const float* z, float* p, int64_t units, const double* scalars, const int* iflags,
-                                hipStream_t st) {
-    hipLaunchKernelGGL(k_pcg_direction, dim3(grid_for(units)), dim3(kVecBlock), 0, st,
-                       reinterpret_cast<const float4*>(z), reinterpret_cast<float4*>(p), units, scalars, iflags);
+    hipLaunchKernelGGL(k_pcg_direction, dim3(g), dim3(kVecBlock), 0, st, (const float4*)v.z, (float4*)v.p, units,
+                       (const double*)partials, it, stop, scalars, row, iflags);
     return hipGetLastError();
 }
 
 hipError_t launch_trial(const float* x, const float* delta, float gamma, int64_t units, int nvox, float* xt,
-                        uint16_t* xb16, hipStream_t st) {
+                        uint16_t* xb16, hipStream_t st, int* done, bool first) {
     hipLaunchKernelGGL(k_trial, dim3(grid_for(units)), dim3(kVecBlock), 0, st, reinterpret_cast<const float4*>(x),
                        reinterpret_cast<const float4*>(delta), gamma, units, nvox, reinterpret_cast<float4*>(xt),
-                       reinterpret_cast<ushort4*>(xb16));
+                       reinterpret_cast<ushort4*>(xb16), done, first);
     return hipGetLastError();
 }
 
