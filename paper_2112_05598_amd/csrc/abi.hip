@@ -342,16 +342,30 @@ int32_t perf_apply_JtJ(perf_scene* s, const void* d_x, const float* d_v, float* 
     return PERF_OK;
 }
 
-static int32_t grad_pass(perf_scene* s, const void* xg, float* grad, float* blocks, bool want_F) {
-    CK(launch_zero(grad, grad ? s->P : 0, s->stream, blocks, blocks ? 5 * s->units : 0));
+// Gradient, blocks and (kind JACOBI or BLOCK4) the preconditioner of the blocks into out.  With four
+// lanes per ray the sums are taken in double in the solve's vectors, which hold nothing between solves.
+static int32_t grad_pass(perf_scene* s, const void* xg, float* grad, float* blocks, int kind, float* out, bool want_F) {
+    const bool in_double = split_rays(M_GRAD, s->geo);
+    double* sums = reinterpret_cast<double*>(s->vz);  // [P] + [units][5]: 72 of the 80 B a unit of vz .. vxt
     RayArgs a = base_args(s);
     a.x = xg;
     a.targets = s->targets;
-    a.y = grad;
+    a.grad = grad;
     a.blocks = blocks;
     a.partials = s->partials;
+    if (in_double) {
+        a.grad = grad ? sums : nullptr;
+        a.blocks = blocks ? sums + s->P : nullptr;
+        CK(launch_zero(s->vz, 2 * (s->P + 5 * s->units), s->stream));
+    } else {
+        CK(launch_zero(grad, grad ? s->P : 0, s->stream, blocks, blocks ? 5 * s->units : 0));
+    }
     CK(launch_ray(M_GRAD, s->desc.param_dtype, s->geo, a, s->stream));
     if (want_F) CK(launch_sum_partials(s->partials, s->n_grad_blocks, 0.5, s->scalars + S_F, s->stream));
+    const bool invert = kind == PERF_PRECOND_JACOBI || kind == PERF_PRECOND_BLOCK4;
+    if (in_double)
+        CK(launch_finish_grad(invert ? kind : PERF_PRECOND_NONE, sums, sums + s->P, s->units, grad, blocks, out, s->stream));
+    else if (invert) CK(launch_precond_invert(kind, blocks, s->units, out, s->stream));
     return PERF_OK;
 }
 
@@ -363,10 +377,9 @@ int32_t perf_build_precond(perf_scene* s, const void* d_x, int32_t kind, float* 
         return fail(PERF_EINVAL, "kind must be NONE, JACOBI or BLOCK4");
     if (kind != PERF_PRECOND_NONE && !d_out) return fail(PERF_EINVAL, "null output");
     float* blocks = d_blocks ? d_blocks : s->blocks;
-    int32_t rc = grad_pass(s, d_x, d_grad, blocks, d_F != nullptr);
+    int32_t rc = grad_pass(s, d_x, d_grad, blocks, kind, d_out, d_F != nullptr);
     if (rc != PERF_OK) return rc;
     if (d_F) CK(hipMemcpyAsync(d_F, s->scalars + S_F, sizeof(double), hipMemcpyDeviceToDevice, s->stream));
-    if (kind != PERF_PRECOND_NONE) CK(launch_precond_invert(kind, blocks, s->units, d_out, s->stream));
     return PERF_OK;
 }
 
@@ -463,7 +476,7 @@ int32_t perf_precond_features(perf_scene* s, const void* d_x, float* d_feat, flo
     if (!s || !d_x || !d_feat) return fail(PERF_EINVAL, "null argument");
     if (!s->feat) return fail(PERF_EUNSUPPORTED, "the scene was created without learned = 1");
     float* blocks = d_blocks ? d_blocks : s->blocks;
-    int32_t rc = grad_pass(s, d_x, nullptr, blocks, false);
+    int32_t rc = grad_pass(s, d_x, nullptr, blocks, PERF_PRECOND_NONE, nullptr, false);
     if (rc != PERF_OK) return rc;
     CK(launch_unit_features(d_x, s->desc.param_dtype, blocks, s->units, d_feat, s->stream));
     return PERF_OK;
@@ -690,15 +703,13 @@ int32_t perf_gn_step(perf_scene* s, float* d_x, const perf_pcg_opts* opts, perf_
         CK(launch_pack_bf16(d_x, s->xb16, s->P, st));
         xg = s->xb16;
     }
-    // 1. gradient b = -J^T r (into vr) and the exact 4x4 blocks, F(x)
     const int kind = opts->precond;
-    int32_t rc = grad_pass(s, xg, s->vr, s->blocks, true);
+    // 1. gradient b = -J^T r (into vr) and the exact 4x4 blocks, F(x)
+    // and 2. the preconditioner (Jacobi and block: the end of the same pass)
+    int32_t rc = grad_pass(s, xg, s->vr, s->blocks, kind, s->minv, true);
     if (rc != PERF_OK) return rc;
     CK(hipEventRecord(ev[1], st));
-    // 2. preconditioner
-    if (kind == PERF_PRECOND_JACOBI || kind == PERF_PRECOND_BLOCK4) {
-        CK(launch_precond_invert(kind, s->blocks, s->units, s->minv, st));
-    } else if (kind == PERF_PRECOND_LEARNED) {
+    if (kind == PERF_PRECOND_LEARNED) {
         rc = learned_minv(s, xg);
         if (rc != PERF_OK) return rc;
         // keep b for a fallback solve: the feature rows (at least P floats) are free now

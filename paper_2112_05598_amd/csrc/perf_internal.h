@@ -87,8 +87,8 @@ struct RayArgs {
     const float* targets;    // [rays][3] (RENDER residuals / GRAD)
     const float* uin;        // [rays][nres] (VJP)
     float* rout;             // [rays][nres] residuals (RENDER with targets) or u (JVP); [rays][3] H otherwise
-    float* y;                // [P] scatter target (VJP / JTJ), gradient (GRAD)
-    float* blocks;           // [units][5] (GRAD)
+    float* y;                // [P] scatter target (VJP / JTJ)
+    void *grad, *blocks;     // [P], [units][5] (GRAD): float, or double where split_rays says so
     double* partials;        // [n_tiles] FP64 sums of r^2
     const int* done;         // skip the launch's work when *done != 0 (PCG stop on device)
     float aux;               // weight lambda of the auxiliary opacity residual (Sec. III-I), 0 = off
@@ -111,6 +111,10 @@ hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, 
 hipError_t launch_zero(float* p, int64_t n, hipStream_t st, float* q = nullptr, int64_t m = 0);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);
 hipError_t launch_sum_partials(const double* partials, int64_t n, double scale, double* out, hipStream_t st);
+// gradient and blocks summed in double (split_rays): rounded to grad and blocks, and the preconditioner
+// of `kind` (NONE, JACOBI, BLOCK4) to out; any output may be null
+hipError_t launch_finish_grad(int kind, const double* grad64, const double* blocks64, int64_t units, float* grad,
+                              float* blocks, float* out, hipStream_t st);
 hipError_t launch_precond_invert(int kind, const float* blocks, int64_t units, float* out, hipStream_t st);
 hipError_t launch_sum_trial(const double* partials, int64_t n, int j, double prev, double* mu, int* done, hipStream_t st);
 struct PcgVectors {

@@ -34,6 +34,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace perf {
 namespace {
 
@@ -270,6 +272,7 @@ __device__ __forceinline__ bool env_hit(const Geo& G, const Ray& r, int l, float
 }
 
 __device__ __forceinline__ void atomic_add(float* p, float v) { unsafeAtomicAdd(p, v); }
+__device__ __forceinline__ void atomic_add(double* p, double v) { unsafeAtomicAdd(p, v); }
 
 // exp(-t) from the hardware base-2 exponential, 2^(-t log2 e): v_exp_f32 is accurate to
 // about an ulp of its result, and rounding t log2 e moves the exponent by at most t ulp,
@@ -678,10 +681,10 @@ struct TexTable {
         wave_fence();
         const int t = keys[l];
         keys[l] = 0;
-        float v[NCH];
+        typename F::Value v[NCH];
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            v[c] = (float)s[c * 64 + l];
+            v[c] = (typename F::Value)s[c * 64 + l];
             s[c * 64 + l] = 0.0;
         }
         wave_fence();
@@ -691,6 +694,7 @@ struct TexTable {
 
 // Global sinks: add a unit's channels to HBM.
 struct SinkY {  // y[4u + c], c < 4
+    typedef float Value;
     float* y;
     __device__ __forceinline__ void operator()(int u, const float* v) const {
         float* p = y + 4 * (size_t)u;
@@ -703,27 +707,30 @@ struct SinkY {  // y[4u + c], c < 4
         atomic_add((float*)((char*)y + (16u * (unsigned)u + 4u * (unsigned)c)), v);
     }
 };
+template <class T>
 struct SinkGrad {  // grad[4u + c] (c < 4) and blocks[5u + c] (channels 4..8)
-    float* grad;
-    float* blocks;
-    __device__ __forceinline__ void operator()(int u, const float* v) const {
+    typedef T Value;
+    T* grad;
+    T* blocks;
+    template <class V>
+    __device__ __forceinline__ void operator()(int u, const V* v) const {
         if (grad) {
-            float* g = grad + 4 * (size_t)u;
+            T* g = grad + 4 * (size_t)u;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if (v[c] != 0.0f) atomic_add(g + c, v[c]);
+                if (v[c] != (V)0) atomic_add(g + c, (T)v[c]);
         }
         if (blocks) {
-            float* b = blocks + 5 * (size_t)u;
+            T* b = blocks + 5 * (size_t)u;
 #pragma unroll
             for (int c = 0; c < 5; ++c)
-                if (v[4 + c] != 0.0f) atomic_add(b + c, v[4 + c]);
+                if (v[4 + c] != (V)0) atomic_add(b + c, (T)v[4 + c]);
         }
     }
-    // one channel of the gradient (32-bit byte offset) or of the block
-    __device__ __forceinline__ void one(bool of_grad, int u, int c, float v) const {
+    // one channel of the gradient or of the block
+    __device__ __forceinline__ void one(bool of_grad, int u, int c, T v) const {
         if (of_grad) {
-            if (grad) atomic_add((float*)((char*)grad + (16u * (unsigned)u + 4u * (unsigned)c)), v);
+            if (grad) atomic_add(grad + 4 * (size_t)u + c, v);
         } else if (blocks) {
             atomic_add(blocks + 5 * (size_t)u + c, v);
         }
@@ -773,8 +780,8 @@ struct GradBrick {
     }
     // Flush the plane at coordinate c of axis A (ring slot rc): the gradient with four lanes per voxel,
     // the blocks with five, so that neighbouring lanes add to neighbouring addresses.
-    template <int A>
-    __device__ __forceinline__ void flush_plane(const Geo& G, int c, int rc, const SinkGrad& out) {
+    template <int A, class Sink>
+    __device__ __forceinline__ void flush_plane(const Geo& G, int c, int rc, const Sink& out) {
         const int n[3] = {G.nx, G.ny, G.nz};
         if (c < 0 || c >= n[A]) return;  // outside the grid nothing is added
         constexpr int P = A == 0 ? 1 : 0, Q = A == 2 ? 1 : 2;
@@ -791,16 +798,16 @@ struct GradBrick {
             const int cp = o[P] + p, cq = o[Q] + q;
             if (v < kW * kW) {
                 lds_double* d = s + (gr ? ch : 4 + ch) * kW3 + pc + place<P>(wrap(p + rs[P])) + place<Q>(wrap(q + rs[Q]));
-                const float f = (float)*d;
+                const typename Sink::Value f = (typename Sink::Value)*d;
                 *d = 0.0;
-                if (f != 0.0f && (unsigned)cp < (unsigned)n[P] && (unsigned)cq < (unsigned)n[Q])
+                if (f != 0 && (unsigned)cp < (unsigned)n[P] && (unsigned)cq < (unsigned)n[Q])
                     out.one(gr, c * pitch[A] + cp * pitch[P] + cq * pitch[Q], ch, f);
             }
         }
         wave_fence();
     }
-    template <int A>
-    __device__ __forceinline__ void move_axis(const Geo& G, int no, const SinkGrad& out) {
+    template <int A, class Sink>
+    __device__ __forceinline__ void move_axis(const Geo& G, int no, const Sink& out) {
         const int d = up[A] ? no - o[A] : o[A] - no;  // never negative
         if (d == 0) return;
         const int cnt = min(d, kW);
@@ -817,7 +824,8 @@ struct GradBrick {
     }
     // Move the window so that the boxes [lo, hi] of every lane that is on lie inside on the side the
     // march goes to.
-    __device__ __forceinline__ void fit(const Geo& G, bool on, const int lo[3], const int hi[3], const SinkGrad& out) {
+    template <class Sink>
+    __device__ __forceinline__ void fit(const Geo& G, bool on, const int lo[3], const int hi[3], const Sink& out) {
         bool in = true;
 #pragma unroll
         for (int a = 0; a < 3; ++a) in &= up[a] ? hi[a] < o[a] + kW : lo[a] >= o[a];
@@ -830,7 +838,8 @@ struct GradBrick {
         move_axis<1>(G, no[1], out);
         move_axis<2>(G, no[2], out);
     }
-    __device__ __forceinline__ void flush_all(const Geo& G, const SinkGrad& out) {
+    template <class Sink>
+    __device__ __forceinline__ void flush_all(const Geo& G, const Sink& out) {
         int rc = rs[2];
 #pragma unroll 1
         for (int t = 0; t < kW; ++t) {
@@ -1458,8 +1467,13 @@ __device__ __forceinline__ void grad_fold(int at, float v[9], unsigned long long
 template <int PD, bool SPLIT>
 __device__ __forceinline__ void grad_scatter(const Geo& G, const Ray& r, bool live, XL<PD> X, const float rr[3],
                                              float r4, float g4, Depth depth, GradBrick& B, TexTable<9>& TT,
-                                             float* __restrict__ grad, float* __restrict__ blocks) {
-    SinkGrad sink{grad, blocks};
+                                             void* grad, void* blocks) {
+    // Four lanes per ray make four times as many waves add to a voxel.  In single precision the order
+    // of their adds would show in the nearly singular blocks (the same step's objective moved by 2e-4 of
+    // itself once in 30), so the sums are taken in double and launch_finish_grad rounds them: two repeats
+    // agree to the last bit but for a tie, for 18 us of a step on 32^3 voxels.
+    typedef typename std::conditional<SPLIT, double, float>::type Value;
+    const SinkGrad<Value> sink{(Value*)grad, (Value*)blocks};
     const float Tx = exp_neg(depth.value());
     float S[3] = {0.0f, 0.0f, 0.0f};
     // environment layers (the four texels of one lookup are distinct units)
@@ -1844,7 +1858,7 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
             }
             // the auxiliary residual's row: d r4 / d sigma_k = g4 delta_k
             const float g4 = -dr4 * Texit;
-            grad_scatter<PD, SPLIT>(G, r, p.active, X, res, p.active ? r4 : 0.0f, g4, depth, B, TT, A.y, A.blocks);
+            grad_scatter<PD, SPLIT>(G, r, p.active, X, res, p.active ? r4 : 0.0f, g4, depth, B, TT, A.grad, A.blocks);
         }
     }
     if constexpr (MODE == M_RENDER || MODE == M_GRAD) {

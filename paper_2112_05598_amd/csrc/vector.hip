@@ -157,27 +157,52 @@ __global__ __launch_bounds__(kSumBlock) void k_sum_trial(const double* p, int64_
 // M^-1 = t^2 = 1/diag(J^T J).  Block: after a ridge rho = 1e-6 max(d, f), t_d = (d + rho)^-1/2,
 // t_f = (f + rho)^-1/2, the normalised coupling e~ = t_d t_f e and 1/s with s = 1 - |e~|^2, the
 // Schur complement of the normalised block [[I, e~], [e~^T, 1]]: (t_d, t_f, e~, 1/s, 0, 0).
+__device__ __forceinline__ void invert_unit(int kind, const float b[5], int64_t u, float* __restrict__ out) {
+    const double d = b[0], e0 = b[1], e1 = b[2], e2 = b[3], f = b[4];
+    if (kind == PERF_PRECOND_JACOBI) {
+        const float td = d > 0.0 ? (float)(1.0 / sqrt(d)) : 0.0f;
+        const float tf = f > 0.0 ? (float)(1.0 / sqrt(f)) : 0.0f;
+        reinterpret_cast<float4*>(out)[u] = make_float4(td, td, td, tf);
+    } else {
+        float4* o = reinterpret_cast<float4*>(out) + 2 * u;
+        const double m = fmax(d, f);
+        if (!(m > 0.0) || !isfinite(d + e0 + e1 + e2 + f)) {  // no ray, or a non-finite block
+            o[0] = o[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            return;
+        }
+        const double rho = 1e-6 * m;
+        const double td = 1.0 / sqrt(d + rho), tf = 1.0 / sqrt(f + rho);
+        const double a0 = e0 * td * tf, a1 = e1 * td * tf, a2 = e2 * td * tf;
+        const double is = 1.0 / (1.0 - (a0 * a0 + a1 * a1 + a2 * a2));
+        o[0] = make_float4((float)td, (float)tf, (float)a0, (float)a1);
+        o[1] = make_float4((float)a2, (float)is, 0.0f, 0.0f);
+    }
+}
+
 __global__ void k_invert(int kind, const float* __restrict__ blocks, int64_t units, float* __restrict__ out) {
     for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < units; u += (int64_t)gridDim.x * blockDim.x) {
-        const float* b = blocks + 5 * u;
-        const double d = b[0], e0 = b[1], e1 = b[2], e2 = b[3], f = b[4];
-        if (kind == PERF_PRECOND_JACOBI) {
-            const float td = d > 0.0 ? (float)(1.0 / sqrt(d)) : 0.0f;
-            const float tf = f > 0.0 ? (float)(1.0 / sqrt(f)) : 0.0f;
-            reinterpret_cast<float4*>(out)[u] = make_float4(td, td, td, tf);
-        } else {
-            float4* o = reinterpret_cast<float4*>(out) + 2 * u;
-            const double m = fmax(d, f);
-            if (!(m > 0.0) || !isfinite(d + e0 + e1 + e2 + f)) {  // no ray, or a non-finite block
-                o[0] = o[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                continue;
-            }
-            const double rho = 1e-6 * m;
-            const double td = 1.0 / sqrt(d + rho), tf = 1.0 / sqrt(f + rho);
-            const double a0 = e0 * td * tf, a1 = e1 * td * tf, a2 = e2 * td * tf;
-            const double is = 1.0 / (1.0 - (a0 * a0 + a1 * a1 + a2 * a2));
-            o[0] = make_float4((float)td, (float)tf, (float)a0, (float)a1);
-            o[1] = make_float4((float)a2, (float)is, 0.0f, 0.0f);
+        float b[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) b[i] = blocks[5 * u + i];
+        invert_unit(kind, b, u, out);
+    }
+}
+
+__global__ void k_finish_grad(int kind, const double* __restrict__ grad64, const double* __restrict__ blocks64,
+                              int64_t units, float* __restrict__ grad, float* __restrict__ blocks,
+                              float* __restrict__ out) {
+    for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < units; u += (int64_t)gridDim.x * blockDim.x) {
+        if (grad) {
+            const double* g = grad64 + 4 * u;
+            float* o = grad + 4 * u;  // (no alignment beyond a float's is asked of the caller)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = (float)g[i];
+        }
+        if (blocks) {
+            float b[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) blocks[5 * u + i] = b[i] = (float)blocks64[5 * u + i];
+            if (out && kind != PERF_PRECOND_NONE) invert_unit(kind, b, u, out);
         }
     }
 }
@@ -515,6 +540,13 @@ hipError_t launch_sum_partials(const double* partials, int64_t n, double scale, 
 
 hipError_t launch_sum_trial(const double* partials, int64_t n, int j, double prev, double* mu, int* done, hipStream_t st) {
     hipLaunchKernelGGL(k_sum_trial, dim3(1), dim3(kSumBlock), 0, st, partials, n, j, prev, mu, done);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish_grad(int kind, const double* grad64, const double* blocks64, int64_t units, float* grad,
+                              float* blocks, float* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_finish_grad, dim3(grid_for(units)), dim3(kVecBlock), 0, st, kind, grad64, blocks64, units, grad,
+                       blocks, out);
     return hipGetLastError();
 }
 
