@@ -145,7 +145,7 @@ Layout make_layout(const perf_scene_desc& d, int n_cams) {
     const int64_t units = (int64_t)d.nx * d.ny * d.nz + (int64_t)d.n_layers * d.env_w * d.env_h;
     const int64_t P = 4 * units;
     const Geo g = make_geo(d, n_cams);
-    L.n_partials = std::max<int64_t>(3 * kVecGrid, std::max(ray_blocks(g, false), ray_blocks(g, true)));
+    L.n_partials = std::max<int64_t>(3 * kVecGrid, std::max(ray_blocks(g, S_ONE), ray_blocks(g, S_FOUR)));
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -345,7 +345,7 @@ int32_t perf_apply_JtJ(perf_scene* s, const void* d_x, const float* d_v, float* 
 // Gradient, blocks and (kind JACOBI or BLOCK4) the preconditioner of the blocks into out.  With four
 // lanes per ray the sums are taken in double in the solve's vectors, which hold nothing between solves.
 static int32_t grad_pass(perf_scene* s, const void* xg, float* grad, float* blocks, int kind, float* out, bool want_F) {
-    const bool in_double = split_rays(M_GRAD, s->geo);
+    const bool in_double = split_rays(M_GRAD, s->geo) != S_ONE;
     double* sums = reinterpret_cast<double*>(s->vz);  // [P] + [units][5]: 72 of the 80 B a unit of vz .. vxt
     RayArgs a = base_args(s);
     a.x = xg;

@@ -11,6 +11,7 @@ namespace perf {
 constexpr int kMaxLayers = PERF_MAX_LAYERS;
 constexpr int kWaves = 2;       // wave64s per ray workgroup
 constexpr int kBlock = 64 * kWaves;
+constexpr int kDeep = 4;        // wave64s per ray workgroup that share their rays (S_DEEP)
 constexpr int kTileX = 16;      // ray workgroup tile: 16 x 8 pixels, each wave an 8x8 half
 constexpr int kTileY = 8;
 constexpr int kVecBlock = 256;  // threads per vector workgroup
@@ -96,10 +97,20 @@ struct RayArgs {
     float thresh;            // RENDER: volume counts as transparent when 1 - T_exit < thresh (0 = off)
 };
 
+// How many lanes march a ray.
+enum Split {
+    S_ONE = 0,   // one lane
+    S_FOUR = 1,  // four lanes, forward4 and adjoint4
+    S_BACK = 2,  // gradient pass only: the four lanes of a ray all run the one-lane forward march and
+                 // share the way back.  A scene's residuals come from one kind of forward march (the render
+                 // pass's) in every pass, so that they agree to the last bit.
+    S_DEEP = 3   // VJP and JTJ: four lanes in each of kDeep waves, which take a piece of the ray's depth each
+};
+
 // workgroups of a ray launch (one partial each): a whole tile per workgroup, or a quarter of it with
 // four lanes per ray (split_rays: the rule launch_ray goes by)
-int64_t ray_blocks(const Geo& g, bool split);
-bool split_rays(int mode, const Geo& g);
+int64_t ray_blocks(const Geo& g, Split split);
+Split split_rays(int mode, const Geo& g);
 // begin, end (both or neither): events that take the kernel's own start and end
 hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st,
                       hipEvent_t begin = nullptr, hipEvent_t end = nullptr);

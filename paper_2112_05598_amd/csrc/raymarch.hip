@@ -1234,9 +1234,38 @@ __device__ __forceinline__ bool env_value(const Geo& G, const Ray& r, int l, boo
     return true;
 }
 
-template <int PD, bool TAN>
+// The layers of a ray, one per slot: layer 4h + t of slot t.  Found once and used in both directions.
+struct EnvHits {
+    static constexpr int kH = kMaxLayers / 4;
+    Tex tx[kH];
+    float al[kH], c[kH][3];
+    bool hit[kH];
+    template <int PD>
+    __device__ __forceinline__ void find(const Geo& G, const Ray& r, bool live, XL<PD> X) {
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            hit[h] = false;
+            al[h] = c[h][0] = c[h][1] = c[h][2] = 0.0f;
+            if (4 * h < G.n_layers) hit[h] = env_value<PD>(G, r, 4 * h + slot_id(), live, X, tx[h], al[h], c[h]);
+        }
+    }
+};
+
+// The piece of a ray's depth that a wave marches: steps j0 .. j1 of the wave, sample j - off of a ray.
+struct Piece {
+    int j0, j1, off;
+    float Hb[3];  // radiance of the pieces behind
+};
+constexpr int kPieceRow = 12;  // floats per ray and piece in LDS
+
+// With DEEP the kDeep waves of a workgroup march the same rays, a piece each, from transmittance 1; the
+// pieces are put together in LDS (shared), front to back.  On return depth is that of the piece's far end.
+// Each wave keeps its own window for the way back, so four times as many windows are flushed; what bounds
+// it is still a step's chain (box, window planes), no longer times the whole ray (split_rays has figures).
+template <int PD, bool TAN, bool DEEP>
 __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, XL<PD> X, VecF4 V, float H[3],
-                                         float& Texit, float& Tdexit, float Hd[3], Depth& depth, float thresh) {
+                                         float& Texit, float& Tdexit, float Hd[3], Depth& depth, float thresh,
+                                         EnvHits& E, Piece& P, float* shared) {
     const int t = slot_id();
     depth.s = 0.0f;
     depth.c = 0.0f;
@@ -1248,7 +1277,17 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
     const float t_min = wave_min_f(r.K > 0 ? r.tn : INFINITY);
     const int off = r.K > 0 ? (int)((r.tn - t_min) / unit + 0.5f) : 0;
     const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
-    for (int j = 0; j < J; j += 4) {
+    const int wave = threadIdx.x >> 6;
+    P.j0 = 0;
+    P.j1 = J;
+    P.off = off;
+    P.Hb[0] = P.Hb[1] = P.Hb[2] = 0.0f;
+    if constexpr (DEEP) {
+        const int len = 4 * ((J + 4 * kDeep - 1) / (4 * kDeep));
+        P.j0 = __builtin_amdgcn_readfirstlane(wave * len);
+        P.j1 = P.j0 + len;
+    }
+    for (int j = P.j0; j < P.j1; j += 4) {
         const int k = j + t - off;
         const bool on = k >= 0 && k < r.K;
         float tau = 0.0f, taud = 0.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, cd0 = 0.0f, cd1 = 0.0f, cd2 = 0.0f;
@@ -1286,7 +1325,54 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
             Hd[2] += k1 * c2 + Ta * cd2;
         }
     }
-    Texit = exp_neg(depth.value());
+    if constexpr (DEEP) {
+        float h[3], hd[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            h[ch] = slot_sum(H[ch]);
+            if constexpr (TAN) hd[ch] = slot_sum(Hd[ch]);
+            H[ch] = Hd[ch] = 0.0f;
+        }
+        const int ray = (lane_id() >> 4) * 4 + (lane_id() & 3);
+        f4* mine = (f4*)(shared + (wave * 16 + ray) * kPieceRow);
+        if (t == 0) {
+            mine[0] = f4{depth.s, depth.c, Vd, h[0]};
+            mine[1] = f4{h[1], h[2], hd[0], hd[1]};
+            mine[2] = f4{hd[2], 0.0f, 0.0f, 0.0f};
+        }
+        __syncthreads();
+        Depth sum{0.0f, 0.0f};
+        Vd = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kDeep; ++w) {
+            const f4* row = (const f4*)(shared + (w * 16 + ray) * kPieceRow);
+            const f4 q0 = row[0], q1 = row[1];
+            const float T = exp_neg(sum.value());
+            const float hw[3] = {T * q0.w, T * q1.x, T * q1.y};
+            if constexpr (TAN) {
+                const float hdw[3] = {q1.z, q1.w, row[2].x};
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) Hd[ch] += T * hdw[ch] - Vd * hw[ch];
+                Vd += q0.z;
+            }
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                H[ch] += hw[ch];
+                if (w > wave) P.Hb[ch] += hw[ch];
+            }
+            sum.add(q0.x);
+            sum.add(-q0.y);
+            if (w == wave) depth = sum;
+        }
+        Texit = exp_neg(sum.value());
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {  // (the slots are summed below)
+            H[ch] = t == 0 ? H[ch] : 0.0f;
+            Hd[ch] = t == 0 ? Hd[ch] : 0.0f;
+        }
+    } else {
+        Texit = exp_neg(depth.value());
+    }
     Tdexit = -Texit * Vd;
     float T = Texit, Td = Tdexit;
     if (thresh > 0.0f && 1.0f - T < thresh) {
@@ -1294,20 +1380,22 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
         H[0] = H[1] = H[2] = 0.0f;
         T = 1.0f;
     }
-    // layers l0 .. l0 + 3, one per lane of the quad
-    for (int l0 = 0; l0 < G.n_layers; l0 += 4) {
-        Tex tx;
-        float al, c[3], ald = 0.0f, cd[3] = {0.0f, 0.0f, 0.0f};
-        const bool hit = env_value<PD>(G, r, l0 + t, live, X, tx, al, c);
+    E.find<PD>(G, r, live, X);
+#pragma unroll
+    for (int h = 0; h < EnvHits::kH; ++h) {
+        if (4 * h >= G.n_layers) continue;
+        const float al = E.al[h];
+        const float(&c)[3] = E.c[h];
+        float ald = 0.0f, cd[3] = {0.0f, 0.0f, 0.0f};
         if constexpr (TAN) {
-            if (hit) {
+            if (E.hit[h]) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float4 w = V(tx.t[q]);
-                    cd[0] += tx.w[q] * w.x;
-                    cd[1] += tx.w[q] * w.y;
-                    cd[2] += tx.w[q] * w.z;
-                    ald += tx.w[q] * w.w;
+                    const float4 w = V(E.tx[h].t[q]);
+                    cd[0] += E.tx[h].w[q] * w.x;
+                    cd[1] += E.tx[h].w[q] * w.y;
+                    cd[2] += E.tx[h].w[q] * w.z;
+                    ald += E.tx[h].w[q] * w.w;
                 }
             }
         }
@@ -1340,72 +1428,75 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
 
 // env_back with one layer per slot; S starts at the background and ends as the radiance seen from
 // the grid exit in every slot.
-template <int PD, class Emit>
-__device__ __forceinline__ void env_back4(const Geo& G, const Ray& r, bool live, XL<PD> X, float Tx, float S[3],
-                                          Emit& emit) {
+template <class Emit>
+__device__ __forceinline__ void env_back4(const Geo& G, const EnvHits& E, float Tx, float S[3], Emit& emit) {
     const int t = slot_id();
-    constexpr int kH = kMaxLayers / 4;
-    Tex tx[kH];
-    float al[kH], c[kH][3], Tl[kH];
-    bool hit[kH];
+    float Tl[EnvHits::kH];
     float T = Tx;
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) S[ch] = G.bg[ch];
 #pragma unroll
-    for (int h = 0; h < kH; ++h) {
-        hit[h] = false;
-        al[h] = Tl[h] = c[h][0] = c[h][1] = c[h][2] = 0.0f;
+    for (int h = 0; h < EnvHits::kH; ++h) {
+        Tl[h] = 0.0f;
         if (4 * h < G.n_layers) {
-            hit[h] = env_value<PD>(G, r, 4 * h + t, live, X, tx[h], al[h], c[h]);
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 Tl[h] = t == s ? T : Tl[h];
-                T *= 1.0f - slot_bcast(al[h], t, s);
+                T *= 1.0f - slot_bcast(E.al[h], t, s);
             }
         }
     }
 #pragma unroll
-    for (int h = kH - 1; h >= 0; --h) {
+    for (int h = EnvHits::kH - 1; h >= 0; --h) {
         if (4 * h < G.n_layers) {
             float Sb[3] = {0.0f, 0.0f, 0.0f};  // radiance behind the own layer
 #pragma unroll
             for (int s = 3; s >= 0; --s) {
-                const float a = slot_bcast(al[h], t, s);
+                const float a = slot_bcast(E.al[h], t, s);
 #pragma unroll
                 for (int ch = 0; ch < 3; ++ch) {
                     Sb[ch] = t == s ? S[ch] : Sb[ch];
-                    S[ch] = a * slot_bcast(c[h][ch], t, s) + (1.0f - a) * S[ch];
+                    S[ch] = a * slot_bcast(E.c[h][ch], t, s) + (1.0f - a) * S[ch];
                 }
             }
-            if (hit[h]) emit(tx[h], c[h], al[h], Tl[h], Sb);
+            if (E.hit[h]) emit(E.tx[h], E.c[h], E.al[h], Tl[h], Sb);
         }
     }
 }
 
-template <int PD>
+template <int PD, bool DEEP>
 __device__ __forceinline__ void adjoint4(const Geo& G, const Ray& r, bool live, XL<PD> X, const float u[3], float q4,
-                                         Depth depth, Brick4& B, TexTable<4>& TT, float* __restrict__ y) {
+                                         float Tx, Depth depth, EnvHits& E, const Piece& P, Brick4& B,
+                                         TexTable<4>& TT, float* __restrict__ y) {
     SinkY sink{y};
     const int t = slot_id();
-    const float Tx = exp_neg(depth.value());
+    const bool last = !DEEP || (threadIdx.x >> 6) == kDeep - 1;  // the wave of the farthest piece adds to the layers
     float S[3];
     auto emit = [&](const Tex& tx, const float c[3], float al, float Tl, const float Sb[3]) {
-        jt_layer(tx, c, al, Tl, Sb, u, TT, sink);
+        if (last) jt_layer(tx, c, al, Tl, Sb, u, TT, sink);
     };
-    env_back4<PD>(G, r, live, X, Tx, S, emit);
+    env_back4(G, E, Tx, S, emit);
     TT.flush(sink);
-    float uG = live ? Tx * (u[0] * S[0] + u[1] * S[1] + u[2] * S[2]) : 0.0f;  // u . G behind the group
-    float Tn = Tx;                                                               // T behind the group
+    // u . G behind the group, and T there
+    float uG = live ? Tx * (u[0] * S[0] + u[1] * S[1] + u[2] * S[2]) : 0.0f;
+    if constexpr (DEEP) uG += u[0] * P.Hb[0] + u[1] * P.Hb[1] + u[2] * P.Hb[2];
+    float Tn = DEEP ? exp_neg(depth.value()) : Tx;
     const int nx = G.nx, nxy = G.nx * G.ny;
     const float unit = G.h * G.step;
-    const float t_max = wave_max_f(r.K > 0 ? r.tf : -INFINITY);
-    const int off = r.K > 0 ? (int)((t_max - r.tf) / unit + 0.5f) : 0;
-    const int J = wave_max_i(r.K > 0 ? off + r.K : 0);
+    int back, J;  // sample back - j - t at step j
+    if constexpr (DEEP) {
+        back = P.j1 - 1 - P.off;
+        J = P.j1 - P.j0;
+    } else {
+        const float t_max = wave_max_f(r.K > 0 ? r.tf : -INFINITY);
+        const int off = r.K > 0 ? (int)((t_max - r.tf) / unit + 0.5f) : 0;
+        back = r.K - 1 + off;
+        J = wave_max_i(r.K > 0 ? off + r.K : 0);
+    }
     B.set_direction(r.gd);
     for (int j = 0; j < J; j += 4) {
-        const int m = j + t - off;
-        const bool on = m >= 0 && m < r.K;
-        const int k = r.K - 1 - m;
+        const int k = back - j - t;
+        const bool on = k >= 0 && k < r.K;
         Corners c{};
         float dk = 0.0f, tau = 0.0f, uc = 0.0f;
         if (on) {
@@ -1466,8 +1557,8 @@ __device__ __forceinline__ void grad_fold(int at, float v[9], unsigned long long
 
 template <int PD, bool SPLIT>
 __device__ __forceinline__ void grad_scatter(const Geo& G, const Ray& r, bool live, XL<PD> X, const float rr[3],
-                                             float r4, float g4, Depth depth, GradBrick& B, TexTable<9>& TT,
-                                             void* grad, void* blocks) {
+                                             float r4, float g4, Depth depth, const EnvHits& E, GradBrick& B,
+                                             TexTable<9>& TT, void* grad, void* blocks) {
     // Four lanes per ray make four times as many waves add to a voxel.  In single precision the order
     // of their adds would show in the nearly singular blocks (the same step's objective moved by 2e-4 of
     // itself once in 30), so the sums are taken in double and launch_finish_grad rounds them: two repeats
@@ -1491,7 +1582,7 @@ __device__ __forceinline__ void grad_scatter(const Geo& G, const Ray& r, bool li
             TT.insert(tx.t[j], v, sink);
         }
     };
-    if constexpr (SPLIT) env_back4<PD>(G, r, live, X, Tx, S, emit);
+    if constexpr (SPLIT) env_back4(G, E, Tx, S, emit);
     else if (live) env_back<PD>(G, r, X, Tx, S, emit);
     TT.flush(sink);
     constexpr int NP = SPLIT ? 1 : 2;     // parities of x and y that a lane holds
@@ -1681,8 +1772,9 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+template <int WAVES>
 __device__ __forceinline__ void block_sum_store(double v, double* out) {
-    __shared__ double red[kWaves];
+    __shared__ double red[WAVES];
     v = wave_sum(v);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane == 0) red[wave] = v;
@@ -1690,7 +1782,7 @@ __device__ __forceinline__ void block_sum_store(double v, double* out) {
     if (threadIdx.x == 0) {
         double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < kWaves; ++i) s += red[i];
+        for (int i = 0; i < WAVES; ++i) s += red[i];
         *out = s;
     }
 }
@@ -1705,25 +1797,29 @@ struct Pix {
 enum Lanes {
     L_LINES = 0,  // 8x8 pixels, a row of 16 lanes holds two lines of 8
     L_PATCH = 1,  // 8x8 pixels, a row of 16 lanes holds a 4x4 patch
-    L_SPLIT = 2   // 4x4 pixels, a row of 16 lanes holds a 2x2 quad four times, once per slot
+    L_SPLIT = 2,  // 4x4 pixels, a row of 16 lanes holds a 2x2 quad four times, once per slot
+    L_DEEP = 3    // the same, and the waves of a workgroup cover the same pixels
 };
 
-// A workgroup covers a tile of one camera, two waves side by side: 16x8 pixels, 8x4 with L_SPLIT.
+// A workgroup covers a tile of one camera, two waves side by side: 16x8 pixels, 8x4 with L_SPLIT; 4x4
+// with L_DEEP.
 template <int LANES>
 __device__ __forceinline__ Pix pixel_of(const Geo& G) {
-    constexpr int kSide = LANES == L_SPLIT ? 4 : 8;  // pixels along a wave's side
+    constexpr bool kQuads = LANES == L_SPLIT || LANES == L_DEEP;
+    constexpr int kSide = kQuads ? 4 : 8;                     // pixels along a wave's side
+    constexpr int kAcross = LANES == L_DEEP ? 1 : kWaves;  // waves side by side
     Pix p;
-    const int tiles_x = LANES == L_SPLIT ? (G.width + 2 * kSide - 1) / (2 * kSide) : G.tiles_x;
-    const int n_tiles = LANES == L_SPLIT ? tiles_x * ((G.height + kSide - 1) / kSide) : G.n_tiles;
+    const int tiles_x = kQuads ? (G.width + kAcross * kSide - 1) / (kAcross * kSide) : G.tiles_x;
+    const int n_tiles = kQuads ? tiles_x * ((G.height + kSide - 1) / kSide) : G.n_tiles;
     const int b = blockIdx.x;
     p.cam = b / n_tiles;
     const int tile = b - p.cam * n_tiles;
     const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = LANES == L_DEEP ? 0 : threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int qx = (lane >> 4) & 1, qy = lane >> 5;
-    const int lx = LANES == L_SPLIT ? qx * 2 + (lane & 1) : LANES == L_PATCH ? qx * 4 + (lane & 3) : lane & 7;
-    const int ly = LANES == L_SPLIT ? qy * 2 + ((lane >> 1) & 1) : LANES == L_PATCH ? qy * 4 + ((lane >> 2) & 3) : lane >> 3;
-    p.px = tx * 2 * kSide + wave * kSide + lx;
+    const int lx = kQuads ? qx * 2 + (lane & 1) : LANES == L_PATCH ? qx * 4 + (lane & 3) : lane & 7;
+    const int ly = kQuads ? qy * 2 + ((lane >> 1) & 1) : LANES == L_PATCH ? qy * 4 + ((lane >> 2) & 3) : lane >> 3;
+    p.px = tx * kAcross * kSide + wave * kSide + lx;
     p.py = ty * kSide + ly;
     p.active = p.px < G.width && p.py < G.height;
     p.ray = ((long long)p.cam * G.height + p.py) * G.width + p.px;
@@ -1737,27 +1833,23 @@ struct Lds {
     static constexpr int WAVES = (MODE == M_VJP || MODE == M_JTJ) ? 4 : MODE == M_GRAD ? 3 : 1;  // waves per SIMD to leave registers for
 };
 
-// How many lanes march a ray.
-enum Split {
-    S_ONE = 0,   // one lane
-    S_FOUR = 1,  // four lanes, forward4 and adjoint4
-    S_BACK = 2   // gradient pass only: the four lanes of a ray all run the one-lane forward march and
-                 // share the way back.  A scene's residuals come from one kind of forward march (the render
-                 // pass's) in every pass, so that they agree to the last bit.
-};
+constexpr int waves_of(int kind) { return kind == S_DEEP ? kDeep : kWaves; }
 
 template <int MODE, int PD, int KIND>
-__global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs A) {
+__global__ __launch_bounds__(64 * waves_of(KIND), Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs A) {
     constexpr int NCH = Lds<MODE>::NCH;
     constexpr bool SCATTER = Lds<MODE>::SCATTER;
     constexpr bool JT = MODE == M_VJP || MODE == M_JTJ;
-    constexpr bool SPLIT = KIND != S_ONE;
-    __shared__ double s_brick[MODE == M_GRAD ? kWaves * NCH * GradBrick::kW3 : 1];
-    __shared__ f4 s_brick4[JT ? kWaves * kB3 : 1];
-    __shared__ f4 s_stage[JT ? kWaves * kStageRow : 1];
+    constexpr bool SPLIT = KIND != S_ONE, DEEP = KIND == S_DEEP;
+    constexpr int kW = waves_of(KIND);
+    __shared__ double s_brick[MODE == M_GRAD ? kW * NCH * GradBrick::kW3 : 1];
+    __shared__ f4 s_brick4[JT ? kW * kB3 : 1];
+    __shared__ f4 s_stage[JT ? kW * kStageRow : 1];
+    __shared__ f4 s_piece[DEEP ? kDeep * 16 * kPieceRow / 4 : 1];
     if (A.done && *A.done) return;
-    const Pix p = pixel_of<SPLIT ? L_SPLIT : MODE == M_GRAD ? L_LINES : L_PATCH>(G);
-    const bool first = !SPLIT || (threadIdx.x & 12) == 0;  // the lane that writes the ray's results
+    const Pix p = pixel_of<DEEP ? L_DEEP : SPLIT ? L_SPLIT : MODE == M_GRAD ? L_LINES : L_PATCH>(G);
+    // the lane that writes the ray's results
+    const bool first = DEEP ? (threadIdx.x & ~51) == 0 : !SPLIT || (threadIdx.x & 12) == 0;
     const int wave = threadIdx.x >> 6;
     const int units = G.nvox + G.n_layers * G.env_w * G.env_h;
     XL<PD> X;
@@ -1770,14 +1862,19 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
     }
     float H[3], Hd[3], Texit, Tdexit;
     Depth depth;
+    EnvHits E;
+    Piece P;
+    float* const shared = (float*)s_piece;
     if constexpr (MODE == M_JVP || MODE == M_JTJ) {
         VecF4 V;
         V.r = make_rsrc(A.v, (unsigned)units * VecF4::kBytes);
-        if constexpr (KIND == S_FOUR) forward4<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f);
+        if constexpr (KIND == S_FOUR || DEEP)
+            forward4<PD, true, DEEP>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f, E, P, shared);
         else forward<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth);
     } else {
         const float thresh = MODE == M_RENDER ? A.thresh : 0.0f;
-        if constexpr (KIND == S_FOUR) forward4<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
+        if constexpr (KIND == S_FOUR || DEEP)
+            forward4<PD, false, DEEP>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh, E, P, shared);
         else forward<PD, false>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
     }
     // auxiliary opacity residual (Sec. III-I, Eq. 10): r4 = lambda (1 - 4 (T - 1/2)^2) =
@@ -1840,7 +1937,7 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
             // u4 d r4 / d sigma_k = u4 dr4/dT (-T delta_k): a per-ray constant times delta_k,
             // added to the sigma partial of every sample
             const float q4 = -u4 * dr4 * Texit;
-            if constexpr (SPLIT) adjoint4<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
+            if constexpr (SPLIT) adjoint4<PD, DEEP>(G, r, p.active, X, u, q4, DEEP ? Texit : exp_neg(depth.value()), depth, E, P, B, TT, A.y);
             else adjoint_scatter<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
         } else {
             static_assert(NCH == GradBrick::kCh && TexTable<NCH>::kDoubles <= NCH * GradBrick::kW3, "the table fits the window");
@@ -1858,11 +1955,12 @@ __global__ __launch_bounds__(kBlock, Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs
             }
             // the auxiliary residual's row: d r4 / d sigma_k = g4 delta_k
             const float g4 = -dr4 * Texit;
-            grad_scatter<PD, SPLIT>(G, r, p.active, X, res, p.active ? r4 : 0.0f, g4, depth, B, TT, A.grad, A.blocks);
+            if constexpr (KIND == S_BACK) E.find<PD>(G, r, p.active, X);
+            grad_scatter<PD, SPLIT>(G, r, p.active, X, res, p.active ? r4 : 0.0f, g4, depth, E, B, TT, A.grad, A.blocks);
         }
     }
     if constexpr (MODE == M_RENDER || MODE == M_GRAD) {
-        if (A.partials) block_sum_store(rr_sum, A.partials + blockIdx.x);
+        if (A.partials) block_sum_store<kW>(rr_sum, A.partials + blockIdx.x);
     }
 }
 
@@ -1924,32 +2022,39 @@ __global__ __launch_bounds__(kBlock) void k_footprint(Geo G, const DevCam* cams,
 
 template <int MODE, int PD, int KIND>
 hipError_t launch_one(const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin, hipEvent_t end) {
-    const unsigned grid = (unsigned)ray_blocks(g, KIND != S_ONE);
+    const unsigned grid = (unsigned)ray_blocks(g, (Split)KIND);
+    const dim3 block(64 * waves_of(KIND));
     if (grid == 0) return hipSuccess;
     // events taken from the dispatch itself: recorded around it they cost 5 us each on the stream
-    if (begin) hipExtLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), dim3(kBlock), 0, st, begin, end, 0, g, a);
-    else hipLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), dim3(kBlock), 0, st, g, a);
+    if (begin) hipExtLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), block, 0, st, begin, end, 0, g, a);
+    else hipLaunchKernelGGL((k_ray<MODE, PD, KIND>), dim3(grid), block, 0, st, g, a);
     return hipGetLastError();
 }
 
 template <int PD, int KIND>
 hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin, hipEvent_t end) {
     switch (mode) {
-        case M_RENDER: return launch_one<M_RENDER, PD, KIND>(g, a, st, begin, end);
-        case M_JVP: return launch_one<M_JVP, PD, KIND>(g, a, st, begin, end);
         case M_VJP: return launch_one<M_VJP, PD, KIND>(g, a, st, begin, end);
         case M_JTJ: return launch_one<M_JTJ, PD, KIND>(g, a, st, begin, end);
-        case M_GRAD:
-            if (KIND == S_FOUR && !split_rays(M_RENDER, g)) return launch_one<M_GRAD, PD, S_BACK>(g, a, st, begin, end);
-            return launch_one<M_GRAD, PD, KIND>(g, a, st, begin, end);
-        default: return hipErrorInvalidValue;
     }
+    if constexpr (KIND != S_DEEP) {
+        switch (mode) {
+            case M_RENDER: return launch_one<M_RENDER, PD, KIND>(g, a, st, begin, end);
+            case M_JVP: return launch_one<M_JVP, PD, KIND>(g, a, st, begin, end);
+            case M_GRAD:
+                if (KIND == S_FOUR && split_rays(M_RENDER, g) == S_ONE)
+                    return launch_one<M_GRAD, PD, S_BACK>(g, a, st, begin, end);
+                return launch_one<M_GRAD, PD, KIND>(g, a, st, begin, end);
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-int64_t ray_blocks(const Geo& g, bool split) {
-    const int64_t w = split ? kTileX / 2 : kTileX, h = split ? kTileY / 2 : kTileY;
+int64_t ray_blocks(const Geo& g, Split split) {
+    const int64_t w = split == S_ONE ? kTileX : split == S_DEEP ? kTileX / 4 : kTileX / 2;
+    const int64_t h = split == S_ONE ? kTileY : kTileY / 2;
     return (int64_t)g.n_cams * ((g.width + w - 1) / w) * ((g.height + h - 1) / h);
 }
 
@@ -1961,20 +2066,30 @@ int64_t ray_blocks(const Geo& g, bool split) {
 //   gradient   400x400: 1250 workgroups 1.74 / 1.62 ms, 2500 3.43 / 3.38, 5000 5.1 / 6.1;
 //              340x340 14.9 / 17.9 ms, 300x300 20.4 / 13.8, 256x256 34 / 15 (S_FOUR)
 //   residuals  400x400: 1250 workgroups 0.21 / 0.16 ms, 2500 0.31 / 0.31, 5000 0.47 / 0.57 at any width
-bool split_rays(int mode, const Geo& g) {
-    const bool scatter = mode == M_VJP || mode == M_JTJ || mode == M_GRAD;
-    const int64_t few = mode == M_VJP || mode == M_JTJ ? 3500 : mode == M_GRAD ? 2000 : 1800;
-    return ray_blocks(g, false) < few || (scatter && g.pitch > 0.6f);
+// Fewer still, and the time is that of the longest rays' chain of steps: the products then share a ray's
+// depth among four waves.  J^T J v, four / sixteen lanes per ray:
+//   32^3, 256 workgroups 0.169 / 0.117 ms; 64^3, 400 0.449 / 0.369, 600 0.442 / 0.396, 1200 0.58 / 0.67;
+//   128^3, 312 0.464 / 0.367, 1250 0.81 / 0.76
+// (the gradient pass gains nothing: a voxel's sums of a ray may not be cut, so the pieces overlap; 32^3
+// 0.300 / 0.311 ms, 64^3 600 workgroups 0.73 / 0.75)
+Split split_rays(int mode, const Geo& g) {
+    const int64_t one = ray_blocks(g, S_ONE);
+    const bool product = mode == M_VJP || mode == M_JTJ;
+    if (product && one < 900) return S_DEEP;
+    const int64_t few = product ? 3500 : mode == M_GRAD ? 2000 : 1800;
+    return one < few || ((product || mode == M_GRAD) && g.pitch > 0.6f) ? S_FOUR : S_ONE;
 }
 
 hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin,
                       hipEvent_t end) {
-    const bool split = split_rays(mode, g);
+    const Split split = split_rays(mode, g);
     if (param_dtype == PERF_BF16)
-        return split ? launch_mode<PERF_BF16, S_FOUR>(mode, g, a, st, begin, end)
-                     : launch_mode<PERF_BF16, S_ONE>(mode, g, a, st, begin, end);
-    return split ? launch_mode<PERF_F32, S_FOUR>(mode, g, a, st, begin, end)
-                 : launch_mode<PERF_F32, S_ONE>(mode, g, a, st, begin, end);
+        return split == S_DEEP   ? launch_mode<PERF_BF16, S_DEEP>(mode, g, a, st, begin, end)
+               : split == S_FOUR ? launch_mode<PERF_BF16, S_FOUR>(mode, g, a, st, begin, end)
+                                 : launch_mode<PERF_BF16, S_ONE>(mode, g, a, st, begin, end);
+    return split == S_DEEP   ? launch_mode<PERF_F32, S_DEEP>(mode, g, a, st, begin, end)
+           : split == S_FOUR ? launch_mode<PERF_F32, S_FOUR>(mode, g, a, st, begin, end)
+                             : launch_mode<PERF_F32, S_ONE>(mode, g, a, st, begin, end);
 }
 
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,
