@@ -38,9 +38,9 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))  # the repository root
 KERNEL_SRC = os.path.join(ROOT, "paper_2112_05598_amd", "csrc", "raymarch.hip")
-JTJ_TAG = "k_ray<3, 0>"  # the J^T J v instantiation of k_ray, FP32 parameters
+JTJ_TAG = "k_ray<3, 0, "  # the J^T J v instantiation of k_ray, FP32 parameters
 COPY_TAGS = ("Mul",)  # the calibration copy: b = a * 1 (reads and writes copy-mib MiB)
-KERNELS = {"k_ray<3, 0>": "jtj", "k_ray<4, 0>": "grad", "k_features": "feat", "k_mlp_infer": "mlp_infer",
+KERNELS = {"k_ray<3, 0, ": "jtj", "k_ray<4, 0, ": "grad", "k_features": "feat", "k_mlp_infer": "mlp_infer",
            "k_mlp_train": "mlp_train"}
 
 

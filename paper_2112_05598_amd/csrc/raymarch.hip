@@ -4,6 +4,7 @@
 // camera and each wave64 an 8x8 half of it.  The lanes of a wave march their rays in step
 // at matched depths, so their trilinear gathers hit the same cache lines and their
 // scatter lands in one small voxel window that the wave combines in LDS before HBM.
+// Where rays are few or pixels wide, four or sixteen lanes share a ray (split_rays).
 //
 // Per ray (Sec. III-A, Eq. 3-4): slab test against the grid box, K = ceil(L / step)
 // samples at the midpoints of equal steps of `step` voxel lengths (the last one shortened
@@ -396,7 +397,9 @@ struct Window {
 // a whole step of the wave with no memory access, no fold and no conflict.  Result register
 // 4b + v of lane l is channel v of voxel (x, y, z) = (l & 3, l >> 2 & 3, l >> 4) of patch b, a float4
 // of one voxel per lane, so a box goes to the LDS window in one conflict-free
-// read-modify-write when the patch's samples leave it.
+// read-modify-write when the patch's samples leave it.  What bounds it is the VALU's issue, 7
+// instructions a sample for the weights beside the matrix instruction's 32 cycles: J^T J v of 16 M
+// rays through 128^3 voxels 43.2 ms, where lanes elected per corner and added in LDS took 72.8.
 struct Brick4 {
     Window win;
     volatile lds_f4* s;  // [kB3]
@@ -751,7 +754,8 @@ struct SinkGrad {  // grad[4u + c] (c < 4) and blocks[5u + c] (channels 4..8)
 // cycles for a wave of distinct addresses and 3 for each lane that shares one.  Only the voxels that
 // leave the rays' register windows have to fit, and 6 voxels along each axis cover 99.6 % of them
 // for an 8x8 tile with pixels 0.47 voxels apart; 15.5 KB a wave leave room for 10 waves per CU (8x8x8
-// voxels took 37 KB, 4 waves).  The rest goes straight to HBM.
+// voxels took 37 KB, 4 waves).  The rest goes straight to HBM.  Gradient and blocks of 40 images of 400x400
+// of 128^3 voxels: 44.3 ms, 84.0 with float sums in 8x8x8 voxels.
 struct GradBrick {
     static constexpr int kW = 6, kW3 = kW * kW * kW, kCh = 9;
     // Place of ring slot r of an axis: the voxels of one parity class (they are added together) are 27
@@ -900,7 +904,9 @@ __device__ __forceinline__ float4 gather4(const L& X, const Corners& c, const Co
 
 // The corners of a lane's cell held in registers from sample to sample.  Slot b holds the corner
 // whose coordinate parities are the bits of b, so a corner that two consecutive cells share stays
-// in its slot and only the others are loaded.
+// in its slot and only the others are loaded: 2.6 of 8 at half-voxel steps.  The L1 looks up about 28
+// lines for a wave's gather of 16 bytes a lane, and that rate had been the limit: the residuals of 16 M
+// rays through 128^3 voxels went from 12.9 to 8.5 ms (VALU issue and the L1 together bound them now).
 struct CellWin {
     int o[3][2];  // unit offset along each axis of the even and of the odd coordinate
     unsigned long long ch[3][2];  // lanes whose even / odd coordinate along an axis changed

@@ -258,12 +258,8 @@ __device__ __forceinline__ bool solve_done(const int* fl) {
     return done != 0;
 }
 
-// An iteration is the product and three launches: p.Ap, the update, the direction.  On a level that fits
-// the caches the vectors cost nothing and the launches 5 us each, so every workgroup sums the partials of
-// the launch before it by itself (2 KB of L2 reads, the same order everywhere) instead of waiting for a
-// launch of one workgroup, and the update clears Ap for the next product: 3 launches where 7 were.  With
-// the product's events taken from its dispatch and one readback, a step of 3 iterations on 32^3 voxels
-// went from 1143 to 1058 us, on 64^3 from 5133 to 4873 us.
+// With one readback, and the product's events taken from its dispatch, a step of 3 iterations on 32^3
+// voxels went from 1143 to 1058 us, on 64^3 from 5133 (5 iterations) to 4873.
 // alpha from the partials of p.Ap; delta += alpha p; r -= alpha Ap; z = M^-1 r; Ap = 0 for the next
 // product; partials of r.r and r.z
 template <int KIND>
