@@ -11,7 +11,6 @@ namespace perf {
 constexpr int kMaxLayers = PERF_MAX_LAYERS;
 constexpr int kWaves = 2;       // wave64s per ray workgroup
 constexpr int kBlock = 64 * kWaves;
-constexpr int kDeep = 4;        // wave64s per ray workgroup that share their rays (S_DEEP)
 constexpr int kTileX = 16;      // ray workgroup tile: 16 x 8 pixels, each wave an 8x8 half
 constexpr int kTileY = 8;
 constexpr int kVecBlock = 256;  // threads per vector workgroup
@@ -104,7 +103,9 @@ enum Split {
     S_BACK = 2,  // gradient pass only: the four lanes of a ray all run the one-lane forward march and
                  // share the way back.  A scene's residuals come from one kind of forward march (the render
                  // pass's) in every pass, so that they agree to the last bit.
-    S_DEEP = 3   // VJP and JTJ: four lanes in each of kDeep waves, which take a piece of the ray's depth each
+    // VJP and JTJ: four lanes in each wave of the workgroup, which take a piece of the ray's depth each
+    S_DEEP = 3,  // four waves
+    S_PAIR = 4   // two
 };
 
 // workgroups of a ray launch (one partial each): a whole tile per workgroup, or a quarter of it with

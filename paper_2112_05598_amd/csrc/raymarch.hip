@@ -1283,14 +1283,15 @@ struct Piece {
 };
 constexpr int kPieceRow = 12;  // floats per ray and piece in LDS
 
-// With DEEP the kDeep waves of a workgroup march the same rays, a piece each, from transmittance 1; the
+// With W > 1 the W waves of a workgroup march the same rays, a piece each, from transmittance 1; the
 // pieces are put together in LDS (shared), front to back.  On return depth is that of the piece's far end.
 // Each wave keeps its own window for the way back, so four times as many windows are flushed; what bounds
 // it is still a step's chain (box, window planes), no longer times the whole ray (split_rays has figures).
-template <int PD, bool TAN, bool DEEP, bool DEPTH = false>
+template <int PD, bool TAN, int W, bool DEPTH = false>
 __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, XL<PD> X, VecF4 V, float H[3],
                                          float& Texit, float& Tdexit, float Hd[3], Depth& depth, float thresh,
                                          EnvHits& E, Piece& P, float* shared) {
+    constexpr bool DEEP = W > 1;
     const int t = slot_id();
     depth.s = 0.0f;
     depth.c = 0.0f;
@@ -1308,7 +1309,7 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
     P.off = off;
     P.Hb[0] = P.Hb[1] = P.Hb[2] = 0.0f;
     if constexpr (DEEP) {
-        const int len = 4 * ((J + 4 * kDeep - 1) / (4 * kDeep));
+        const int len = 4 * ((J + 4 * W - 1) / (4 * W));
         P.j0 = __builtin_amdgcn_readfirstlane(wave * len);
         P.j1 = P.j0 + len;
     }
@@ -1375,7 +1376,7 @@ __device__ __forceinline__ void forward4(const Geo& G, const Ray& r, bool live, 
         Depth sum{0.0f, 0.0f};
         Vd = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kDeep; ++w) {
+        for (int w = 0; w < W; ++w) {
             const f4* row = (const f4*)(shared + (w * 16 + ray) * kPieceRow);
             const f4 q0 = row[0], q1 = row[1];
             const float T = exp_neg(sum.value());
@@ -1495,13 +1496,14 @@ __device__ __forceinline__ void env_back4(const Geo& G, const EnvHits& E, float 
     }
 }
 
-template <int PD, bool DEEP>
+template <int PD, int W>
 __device__ __forceinline__ void adjoint4(const Geo& G, const Ray& r, bool live, XL<PD> X, const float u[3], float q4,
                                          float Tx, Depth depth, EnvHits& E, const Piece& P, Brick4& B,
                                          TexTable<4>& TT, float* __restrict__ y) {
+    constexpr bool DEEP = W > 1;
     SinkY sink{y};
     const int t = slot_id();
-    const bool last = !DEEP || (threadIdx.x >> 6) == kDeep - 1;  // the wave of the farthest piece adds to the layers
+    const bool last = !DEEP || (threadIdx.x >> 6) == W - 1;  // the wave of the farthest piece adds to the layers
     float S[3];
     auto emit = [&](const Tex& tx, const float c[3], float al, float Tl, const float Sb[3]) {
         if (last) jt_layer(tx, c, al, Tl, Sb, u, TT, sink);
@@ -1864,19 +1866,19 @@ struct Lds {
     static constexpr int WAVES = (MODE == M_VJP || MODE == M_JTJ) ? 4 : MODE == M_GRAD ? 3 : 1;  // waves per SIMD to leave registers for
 };
 
-constexpr int waves_of(int kind) { return kind == S_DEEP ? kDeep : kWaves; }
+constexpr int waves_of(int kind) { return kind == S_DEEP ? 4 : kind == S_PAIR ? 2 : kWaves; }
 
 template <int MODE, int PD, int KIND>
 __global__ __launch_bounds__(64 * waves_of(KIND), Lds<MODE>::WAVES) void k_ray(Geo G, RayArgs A) {
     constexpr int NCH = Lds<MODE>::NCH;
     constexpr bool SCATTER = Lds<MODE>::SCATTER;
     constexpr bool JT = MODE == M_VJP || MODE == M_JTJ;
-    constexpr bool SPLIT = KIND != S_ONE, DEEP = KIND == S_DEEP;
-    constexpr int kW = waves_of(KIND);
+    constexpr bool SPLIT = KIND != S_ONE, DEEP = KIND == S_DEEP || KIND == S_PAIR;
+    constexpr int kW = waves_of(KIND), kShare = DEEP ? kW : 1;  // waves, and those that share their rays
     __shared__ double s_brick[MODE == M_GRAD ? kW * NCH * GradBrick::kW3 : 1];
     __shared__ f4 s_brick4[JT ? kW * kB3 : 1];
     __shared__ f4 s_stage[JT ? kW * kStageRow : 1];
-    __shared__ f4 s_piece[DEEP ? kDeep * 16 * kPieceRow / 4 : 1];
+    __shared__ f4 s_piece[DEEP ? kW * 16 * kPieceRow / 4 : 1];
     if (A.done && *A.done) return;
     const Pix p = pixel_of<DEEP ? L_DEEP : SPLIT ? L_SPLIT : MODE == M_GRAD ? L_LINES : L_PATCH>(G);
     // the lane that writes the ray's results
@@ -1900,12 +1902,12 @@ __global__ __launch_bounds__(64 * waves_of(KIND), Lds<MODE>::WAVES) void k_ray(G
         VecF4 V;
         V.r = make_rsrc(A.v, (unsigned)units * VecF4::kBytes);
         if constexpr (KIND == S_FOUR || DEEP)
-            forward4<PD, true, DEEP>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f, E, P, shared);
+            forward4<PD, true, kShare>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth, 0.0f, E, P, shared);
         else forward<PD, true>(G, r, p.active, X, V, H, Texit, Tdexit, Hd, depth);
     } else {
         const float thresh = MODE == M_RENDER ? A.thresh : 0.0f;
         if constexpr (KIND == S_FOUR || DEEP)
-            forward4<PD, false, DEEP, MODE == M_VJP && !DEEP>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh, E, P, shared);
+            forward4<PD, false, kShare, MODE == M_VJP && !DEEP>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh, E, P, shared);
         else forward<PD, false, MODE == M_VJP>(G, r, p.active, X, VecF4{}, H, Texit, Tdexit, Hd, depth, thresh);
     }
     // auxiliary opacity residual (Sec. III-I, Eq. 10): r4 = lambda (1 - 4 (T - 1/2)^2) =
@@ -1968,7 +1970,7 @@ __global__ __launch_bounds__(64 * waves_of(KIND), Lds<MODE>::WAVES) void k_ray(G
             // u4 d r4 / d sigma_k = u4 dr4/dT (-T delta_k): a per-ray constant times delta_k,
             // added to the sigma partial of every sample
             const float q4 = -u4 * dr4 * Texit;
-            if constexpr (SPLIT) adjoint4<PD, DEEP>(G, r, p.active, X, u, q4, DEEP ? Texit : exp_neg(depth.value()), depth, E, P, B, TT, A.y);
+            if constexpr (SPLIT) adjoint4<PD, kShare>(G, r, p.active, X, u, q4, DEEP ? Texit : exp_neg(depth.value()), depth, E, P, B, TT, A.y);
             else adjoint_scatter<PD>(G, r, p.active, X, u, q4, depth, B, TT, A.y);
         } else {
             static_assert(NCH == GradBrick::kCh && TexTable<NCH>::kDoubles <= NCH * GradBrick::kW3, "the table fits the window");
@@ -2068,7 +2070,7 @@ hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st,
         case M_VJP: return launch_one<M_VJP, PD, KIND>(g, a, st, begin, end);
         case M_JTJ: return launch_one<M_JTJ, PD, KIND>(g, a, st, begin, end);
     }
-    if constexpr (KIND != S_DEEP) {
+    if constexpr (KIND != S_DEEP && KIND != S_PAIR) {
         switch (mode) {
             case M_RENDER: return launch_one<M_RENDER, PD, KIND>(g, a, st, begin, end);
             case M_JVP: return launch_one<M_JVP, PD, KIND>(g, a, st, begin, end);
@@ -2081,10 +2083,20 @@ hipError_t launch_mode(int mode, const Geo& g, const RayArgs& a, hipStream_t st,
     return hipErrorInvalidValue;
 }
 
+template <int PD>
+hipError_t launch_split(int mode, const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin, hipEvent_t end) {
+    switch (split_rays(mode, g)) {
+        case S_DEEP: return launch_mode<PD, S_DEEP>(mode, g, a, st, begin, end);
+        case S_PAIR: return launch_mode<PD, S_PAIR>(mode, g, a, st, begin, end);
+        case S_FOUR: return launch_mode<PD, S_FOUR>(mode, g, a, st, begin, end);
+        default: return launch_mode<PD, S_ONE>(mode, g, a, st, begin, end);
+    }
+}
+
 }  // namespace
 
 int64_t ray_blocks(const Geo& g, Split split) {
-    const int64_t w = split == S_ONE ? kTileX : split == S_DEEP ? kTileX / 4 : kTileX / 2;
+    const int64_t w = split == S_ONE ? kTileX : split == S_DEEP || split == S_PAIR ? kTileX / 4 : kTileX / 2;
     const int64_t h = split == S_ONE ? kTileY : kTileY / 2;
     return (int64_t)g.n_cams * ((g.width + w - 1) / w) * ((g.height + h - 1) / h);
 }
@@ -2098,29 +2110,25 @@ int64_t ray_blocks(const Geo& g, Split split) {
 //              340x340 14.9 / 17.9 ms, 300x300 20.4 / 13.8, 256x256 34 / 15 (S_FOUR)
 //   residuals  400x400: 1250 workgroups 0.21 / 0.16 ms, 2500 0.31 / 0.31, 5000 0.47 / 0.57 at any width
 // Fewer still, and the time is that of the longest rays' chain of steps: the products then share a ray's
-// depth among four waves.  J^T J v, four / sixteen lanes per ray:
-//   32^3, 256 workgroups 0.169 / 0.117 ms; 64^3, 400 0.449 / 0.369, 600 0.442 / 0.396, 1200 0.58 / 0.67;
-//   128^3, 312 0.464 / 0.367, 1250 0.81 / 0.76
+// depth among the two or four waves of a workgroup.  J^T J v, ms with one, two, four waves:
+//   32^3, 256 workgroups (of S_ONE) 0.169 0.128 0.117; 128^3, 312 0.464 0.379 0.366
+//   64^3, 400 0.449 0.369 0.373; 600 0.442 0.372 0.397; 1200 0.582 0.562 0.653; 1800 0.811 0.805; 2400 0.98 1.01
+//   128^3, 1250 0.812 0.681 0.756; 1800 1.00 0.90; 2500 1.59 1.48
 // (the gradient pass gains nothing: a voxel's sums of a ray may not be cut, so the pieces overlap; 32^3
 // 0.300 / 0.311 ms, 64^3 600 workgroups 0.73 / 0.75)
 Split split_rays(int mode, const Geo& g) {
     const int64_t one = ray_blocks(g, S_ONE);
     const bool product = mode == M_VJP || mode == M_JTJ;
-    if (product && one < 900) return S_DEEP;
+    if (product && one < 350) return S_DEEP;
+    if (product && one < 2000) return S_PAIR;
     const int64_t few = product ? 3500 : mode == M_GRAD ? 2000 : 1800;
     return one < few || ((product || mode == M_GRAD) && g.pitch > 0.6f) ? S_FOUR : S_ONE;
 }
 
 hipError_t launch_ray(int mode, int param_dtype, const Geo& g, const RayArgs& a, hipStream_t st, hipEvent_t begin,
                       hipEvent_t end) {
-    const Split split = split_rays(mode, g);
-    if (param_dtype == PERF_BF16)
-        return split == S_DEEP   ? launch_mode<PERF_BF16, S_DEEP>(mode, g, a, st, begin, end)
-               : split == S_FOUR ? launch_mode<PERF_BF16, S_FOUR>(mode, g, a, st, begin, end)
-                                 : launch_mode<PERF_BF16, S_ONE>(mode, g, a, st, begin, end);
-    return split == S_DEEP   ? launch_mode<PERF_F32, S_DEEP>(mode, g, a, st, begin, end)
-           : split == S_FOUR ? launch_mode<PERF_F32, S_FOUR>(mode, g, a, st, begin, end)
-                             : launch_mode<PERF_F32, S_ONE>(mode, g, a, st, begin, end);
+    return param_dtype == PERF_BF16 ? launch_split<PERF_BF16>(mode, g, a, st, begin, end)
+                                    : launch_split<PERF_F32>(mode, g, a, st, begin, end);
 }
 
 hipError_t launch_footprint(const Geo& g, const DevCam* cams, int32_t* per_ray, unsigned long long* totals,

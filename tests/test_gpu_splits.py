@@ -1,7 +1,7 @@
 """The ways a launch is divided, at the sizes where one gives way to the next, against the FP64 oracle.
 
 * rays: many cameras of 9x5 pixels, one workgroup each, so that every march runs with one lane per ray,
-  four, and sixteen; wide pixels; up to eight layers; the opacity residual and jittered samples;
+  four, eight and sixteen; wide pixels; up to eight layers; the opacity residual and jittered samples;
 * a value that is not finite stays in the voxels and texels its ray touches;
 * the line search, whose trials are enqueued four at a time;
 * the learned preconditioner's training rows, 32 to a wave and 256 to a workgroup, and its units;
@@ -42,7 +42,8 @@ RADII = tuple(2.0 + 0.5 * i for i in range(8))
 RAYS = [(899, 14.0, 1, 0.0, 0, "f32"), (900, 14.0, 8, 0.1, 3, "f32"), (1799, 14.0, 5, 0.0, 0, "bf16"),
         (1800, 14.0, 2, 0.1, 0, "f32"), (2000, 14.0, 2, 0.0, 5, "f32"), (3500, 14.0, 8, 0.1, 3, "f32"),
         (3500, 14.0, 2, 0.0, 0, "bf16"), (3500, 60.0, 3, 0.1, 0, "f32"), (40, 60.0, 8, 0.1, 3, "bf16"),
-        (1, 60.0, 0, 0.0, 0, "f32")]
+        (1, 60.0, 0, 0.0, 0, "f32"), (349, 14.0, 8, 0.1, 3, "f32"), (350, 14.0, 1, 0.0, 5, "bf16"),
+        (350, 60.0, 8, 0.1, 0, "f32"), (1999, 14.0, 3, 0.1, 3, "f32")]
 
 
 class Rays:
@@ -89,7 +90,7 @@ def test_marches(rays):
     assert abs(F.item() - F_or) <= 1e-5 * F_or
 
 
-@pytest.mark.parametrize("n", [30, 1000, 3500])
+@pytest.mark.parametrize("n", [30, 1000, 2000, 3500])
 def test_nonfinite_stays_in_its_corners(n):
     s = Rays(n, 14.0, 2, 0.0, 0, "f32")
     u = ps.random_vector(3 * s.sc.n_rays, 4)
