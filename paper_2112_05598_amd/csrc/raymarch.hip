@@ -399,7 +399,7 @@ struct Window {
 // of one voxel per lane, so a box goes to the LDS window in one conflict-free
 // read-modify-write when the patch's samples leave it.  What bounds it is the VALU's issue, 7
 // instructions a sample for the weights beside the matrix instruction's 32 cycles: J^T J v of 16 M
-// rays through 128^3 voxels 43.2 ms, where lanes elected per corner and added in LDS took 72.8.
+// rays through 128^3 voxels 41.7 ms, where lanes elected per corner and added in LDS took 72.8.
 struct Brick4 {
     Window win;
     volatile lds_f4* s;  // [kB3]
@@ -590,7 +590,11 @@ struct Brick4 {
         bool fits = want && in_box(rg);
         const unsigned long long miss = __ballot(want && !fits);
         if (miss) {
-            rebase(G, rows_of(miss), want, c.g, out);
+            // every patch with a sample moves along: the moves then come together, once in a few steps of the
+            // wave, where a move of each patch by itself cost its chain of minima, scalar tests and window
+            // moves four times (J^T J v of 16 M rays through 128^3 voxels 43.1 against 41.7 ms; only the
+            // patches about to leave as well, 42.1)
+            rebase(G, rows_of(__ballot(want)), want, c.g, out);
 #pragma unroll
             for (int a = 0; a < 3; ++a) rg[a] = c.g[a] - fb[a];
             fits = want && in_box(rg);
