@@ -108,8 +108,8 @@ enum Split {
     S_PAIR = 4   // two
 };
 
-// workgroups of a ray launch (one partial each): a whole tile per workgroup, or a quarter of it with
-// four lanes per ray (split_rays: the rule launch_ray goes by)
+// workgroups of a ray launch (one partial each): a whole tile per workgroup, a quarter of it with
+// four lanes per ray, an eighth where waves share their rays (split_rays: the rule launch_ray goes by)
 int64_t ray_blocks(const Geo& g, Split split);
 Split split_rays(int mode, const Geo& g);
 // begin, end (both or neither): events that take the kernel's own start and end
